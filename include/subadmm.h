@@ -197,14 +197,17 @@ enum subadmm_option {
   /* Iteration path of subadmm_solve / subadmm_rigid_step: 0 (default) = one workgroup per
    * scene (the kernel forms above) when every scene fits it (at most 512 slot rows and 512
    * interfaces, slot vectors in LDS), else the large-scene path; 1 = always the large-scene
-   * path; 2 = always its phase form.  The large-scene path keeps the slot vectors and reads
-   * the operators in device memory.  Scenes of at most 2048 slot rows run it with one
-   * workgroup per scene in one launch (workgroup barriers between the phases); larger ones
-   * (single coupled scenes of thousands of subsystems) run one launch per phase of each
-   * iteration over all scenes (x-update per slot row, residual and stopping test per
-   * scene, z-update per interface), and eager steps stop launching once every scene has
-   * stopped (checked every 32 iterations).  Both forms compute the same iteration bit for
-   * bit; scenes stop independently.  The learned start and subadmm_rigid_steps need the
+   * path's one-workgroup or phase form; 2 = always its phase form.  The large-scene path
+   * (value 0) cuts every scene into several workgroups that keep their part of the
+   * operators on chip and exchange the rows they share in one launch, when the interfaces
+   * have one or two members, the parts fit and the device holds every workgroup at once.
+   * Otherwise it keeps the slot vectors and reads the operators in device memory: scenes of
+   * at most 2048 slot rows with one workgroup per scene in one launch (workgroup barriers
+   * between the phases), larger ones with one launch per phase of each iteration over all
+   * scenes (x-update per slot row, residual and stopping test per scene, z-update per
+   * interface), where eager steps stop launching once every scene has stopped (checked
+   * every 32 iterations).  All forms compute the same iteration bit for bit; scenes stop
+   * independently.  The learned start and subadmm_rigid_steps need the
    * per-scene kernel. */
   SUBADMM_OPT_LARGE_PATH = 8,
   /* 1 = after every solve and rigid step (subadmm_solve, subadmm_solve_scratch,
@@ -322,7 +325,9 @@ int subadmm_solve(subadmm_problem* p, const void* A, const void* b, const void* 
  * size classes run one after another on it.  Calls no allocating routine.  Inputs and
  * outputs as subadmm_solve; warm COLD or GIVEN only.  stats_out (host, n_scene entries,
  * may be NULL) receives the per-scene statistics and then the call synchronises the
- * stream.  E_WORKSPACE if subadmm_workspace_bytes(p) exceeds SUBADMM_SCRATCH_BYTES.
+ * stream.  E_WORKSPACE if the tables and per-step arrays it needs exceed
+ * SUBADMM_SCRATCH_BYTES (subadmm_workspace_bytes(p) less the exchange buffers of scenes cut
+ * into several workgroups, which this call does not use).
  * Every call on one GPU shares that GPU's array and overwrites it: calls that overlap on
  * one GPU (other streams, other threads) race and must be serialised by the caller. */
 #define SUBADMM_SCRATCH_BYTES ((size_t)32 << 20)

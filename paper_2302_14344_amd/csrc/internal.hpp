@@ -206,6 +206,36 @@ struct LargeArgs {
   int64_t n_slot, n_dof;
 };
 
+// The iteration of large scenes cut into several workgroups each, exchanging through polled
+// buffers (interfaces of one or two members).
+constexpr int kClusterThreads = 512;     // threads per workgroup; interfaces per workgroup at most
+constexpr int kClusterRows = 1024;       // slot rows per workgroup at most
+constexpr size_t kClusterLds = 144 * 1024;
+constexpr int kClusterWordsF32 = 1, kClusterWordsF64 = 2;  // exchange words per value
+template <typename T>
+struct ClusterArgs {
+  LargeArgs<T> g;            // y, u, w keep the start values; statistics and outputs as there
+  const int32_t* wg;         // 8 per workgroup: scene, first and end subsystem, its range of
+                             // if_list, the scene's first workgroup, its workgroups, own index
+  const int32_t* order;      // workgroup of each block
+  const int32_t* if_list;    // interfaces touching each workgroup's subsystems
+  const int32_t* bidx;       // per slot row: index among the exchanged rows, -1 for the others
+  unsigned long long* ybuf;  // 2 x n_ex values: y of the exchanged rows by iteration parity
+  unsigned long long* part;  // 2 x n_wg x 4 words: residual partials
+  int32_t* lost;             // per scene: a wait expired
+  uint32_t* epoch;           // tag base of this launch
+  long long wait_ticks;      // longest wait, in ticks of the 100 MHz clock
+  int64_t n_ex;
+  int32_t n_wg;
+};
+
+// What decides the cluster kernel's form and LDS: the most columns of an operator row, the
+// most slot rows of a workgroup, its dynamic LDS with the operators and without them.
+struct ClusterShape {
+  int max_nc = 0, rows = 0;
+  size_t lds = 0, lds_w = 0;
+};
+
 // Constraint error of a step (the accuracy measure), per scene.
 template <typename T>
 struct ErrorArgs {
@@ -365,6 +395,12 @@ hipError_t launch_large_loop(const LargeArgs<T>& a, hipStream_t s, int poll_ever
 // launch)
 template <typename T>
 hipError_t launch_large_scene(const LargeArgs<T>& a, int threads, hipStream_t s);
+// the same iteration with several workgroups per scene, then the tail kernel.
+// cluster_capacity: workgroups of that shape the device holds at once.
+template <typename T>
+hipError_t launch_cluster(const ClusterArgs<T>& a, const ClusterShape& c, int tail_threads, hipStream_t s);
+template <typename T>
+hipError_t cluster_capacity(const ClusterShape& c, int* wgs);
 // ADMM's primal and dual residuals of the returned (z_in, u_in), per scene (large-scene
 // slot arrays as scratch)
 template <typename T>

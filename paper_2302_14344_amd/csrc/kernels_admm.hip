@@ -15,6 +15,8 @@
 //     block reduction) -> stopping test -> z-update (Eq. 16-21) -> dual update (Eq. 14).
 //   After a z-update u_i,j = -lambda_j and w = beta z - u = y + 2 lambda, so the kernel
 //   keeps (y, w, u) per slot row.
+#include <type_traits>
+
 #include "internal.hpp"
 #include "rigid_device.hpp"
 
@@ -1726,17 +1728,33 @@ __global__ void __launch_bounds__(256) large_final_kernel(LargeArgs<T> a) {
 // z-update as the phase kernels, with workgroup barriers in place of kernel boundaries, on
 // the same global slot arrays.  Bitwise equal to the phase kernels.
 template <typename T>
-__global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
-  __shared__ double red[2][4];
-  __shared__ int stop;
-  const int sc = blockIdx.x;
+__device__ inline void large_scene_iterate(const LargeArgs<T>& a, const int sc, double (*red)[4], int* stop) {
   const LoopArgs<T>& l = a.l;
   const int tid = threadIdx.x, bd = blockDim.x;
   const int s0 = l.t.sc_slot[sc], s1 = l.t.sc_slot[sc + 1];
   const int i0 = l.t.sc_if[sc], i1 = l.t.sc_if[sc + 1];
   const int d0 = l.t.sc_dof[sc], d1 = l.t.sc_dof[sc + 1];
-  if (tid == 0) a.done[sc] = 0;
-  for (int g = s0 + tid; g < s1; g += bd) {
+  for (int it = 0; it < l.max_iters; ++it) {
+    for (int g = s0 + tid; g < s1; g += bd) large_xupdate_row<T>(a, g);
+    __syncthreads();
+    if (large_residual_scene<T>(a, sc, it, red, stop)) break;
+    for (int j = i0 + tid; j < i1; j += bd) large_zupdate_if<T>(a, j);
+    __syncthreads();
+  }
+  for (int g = d0 + tid; g < d1; g += bd) large_final_item<T>(a, g, true, false, false);
+  for (int g = s0 + tid; g < s1; g += bd) large_final_item<T>(a, g, false, true, false);
+  for (int j = i0 + tid; j < i1; j += bd) large_final_item<T>(a, j, false, false, true);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
+  __shared__ double red[2][4];
+  __shared__ int stop;
+  const int sc = blockIdx.x;
+  const LoopArgs<T>& l = a.l;
+  const int s0 = l.t.sc_slot[sc], s1 = l.t.sc_slot[sc + 1];
+  if (threadIdx.x == 0) a.done[sc] = 0;
+  for (int g = s0 + threadIdx.x; g < s1; g += blockDim.x) {
     const T be = l.beta[l.t.slot_sub[g]];
     const T z0 = l.z_in ? l.z_in[g] : (T)0;
     const T u0 = l.u_in ? l.u_in[g] : (T)0;
@@ -1745,17 +1763,592 @@ __global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
     a.u[g] = u0;
   }
   __syncthreads();
-  for (int it = 0; it < l.max_iters; ++it) {
-    for (int g = s0 + tid; g < s1; g += bd) large_xupdate_row<T>(a, g);
+  large_scene_iterate<T>(a, sc, red, &stop);
+}
+
+// ------------------------------------------------------------------------------------
+// Large scenes, several workgroups per scene in one launch.  The host cuts every scene into
+// runs of consecutive subsystems; a workgroup keeps its run's operators H_i in LDS (the
+// blocked layout of loop_kernel), its slot vectors too, one interface per thread in
+// registers, and iterates without kernel boundaries.  Per iteration the workgroups of a
+// scene exchange the y of the interfaces that join two of them (both compute that
+// interface's z-update from the same y) and the residual partials.
+//
+// Exchange: every value travels as 64-bit words of 32 data bits and a 32-bit tag, stored and
+// loaded with agent-scope relaxed atomics (coherent across the XCDs' L2s); the tag names the
+// launch and the iteration, so a word validates itself and a reader polls the word it needs.
+// Two buffers in turn: a workgroup stores iteration l + 2 only after it has seen every
+// partial of l + 1, and a partial of l + 1 is stored after its workgroup has read all it
+// needs of l.  Tags start at a counter in device memory that the tail kernel advances after
+// each launch (so replays of a captured launch use fresh tags).
+//
+// The grid fits the device (checked at bind), but another stream's kernels may hold CUs, so
+// every wait is bounded: when it expires the workgroup marks the scene lost and leaves, and
+// the tail kernel runs that scene again from its start values (kept in y, u, w) with one
+// workgroup.  Per-row and per-interface arithmetic and its order are those of the phase
+// kernels, so v_hat, lambda, z and u are the same bits.
+//
+// Bound by latency: one exchange through the coherent point and the three workgroup barriers
+// around it per iteration, ~2.7 us, against the phase kernels' three launches (~20 us) or one
+// workgroup reading the operators from device memory (10.2 us).  Measured per launch of the
+// iteration, FP32: the 640-segment cable at 60 iterations 1180 -> 183 us, the stirring of 216
+// spheres at 60 iterations 1030 -> 181 us, 64 mixed scenes at 100 iterations 1020 -> 276 us.
+// All loads of a poll are in flight together and the z-update runs three rows wide unless the
+// wave holds a larger interface (with a wait per value and all waves six wide: 4.2 us).
+// ------------------------------------------------------------------------------------
+template <typename T>
+struct Tagged;
+template <>
+struct Tagged<float> {
+  static constexpr int N = kClusterWordsF32;
+  __device__ static void put(unsigned long long* p, float v, uint32_t tag) {
+    const unsigned long long x = ((unsigned long long)__float_as_uint(v) << 32) | tag;
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ static bool get(const unsigned long long* p, float* v, uint32_t tag) {
+    const unsigned long long x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *v = __uint_as_float((uint32_t)(x >> 32));
+    return (uint32_t)x == tag;
+  }
+};
+template <>
+struct Tagged<double> {
+  static constexpr int N = kClusterWordsF64;
+  __device__ static void put(unsigned long long* p, double v, uint32_t tag) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    __hip_atomic_store(p, (b & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, (b << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ static bool get(const unsigned long long* p, double* v, uint32_t tag) {
+    const unsigned long long h = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long l = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *v = __longlong_as_double((long long)((h & 0xffffffff00000000ull) | (l >> 32)));
+    return (uint32_t)h == tag && (uint32_t)l == tag;
+  }
+};
+
+// x_r of one slot row from the blocked layout in the order of large_xupdate_row: column c
+// goes to partial sum c mod 4 while a full group of four remains, the rest to partial 0 (the
+// zero padding beyond the last column adds zeros).
+__device__ inline float cluster_row_dot(const float4* Hv, const float4* Wv, int nc, int hs) {
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  const int nq = nc >> 2;
+  int q = 0;
+  for (; q + 3 < nq; q += 4) {
+    float4 h[4], w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      h[k] = Hv[(q + k) * hs];
+      w[k] = Wv[q + k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      acc[0] = zfma(h[k].x, w[k].x, acc[0]);
+      acc[1] = zfma(h[k].y, w[k].y, acc[1]);
+      acc[2] = zfma(h[k].z, w[k].z, acc[2]);
+      acc[3] = zfma(h[k].w, w[k].w, acc[3]);
+    }
+  }
+  for (; q < nq; ++q) {
+    const float4 h = Hv[q * hs], w = Wv[q];
+    acc[0] = zfma(h.x, w.x, acc[0]);
+    acc[1] = zfma(h.y, w.y, acc[1]);
+    acc[2] = zfma(h.z, w.z, acc[2]);
+    acc[3] = zfma(h.w, w.w, acc[3]);
+  }
+  if (nc & 3) {
+    const float4 h = Hv[nq * hs], w = Wv[nq];
+    acc[0] = zfma(h.z, w.z, zfma(h.y, w.y, zfma(h.x, w.x, acc[0])));
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+__device__ inline double cluster_row_dot(const double2* Hv, const double2* Wv, int nc, int hs) {
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  const int nq = (nc >> 2) * 2;
+  for (int q = 0; q < nq; q += 2) {
+    const double2 h0 = Hv[q * hs], w0 = Wv[q], h1 = Hv[(q + 1) * hs], w1 = Wv[q + 1];
+    acc[0] = zfma(h0.x, w0.x, acc[0]);
+    acc[1] = zfma(h0.y, w0.y, acc[1]);
+    acc[2] = zfma(h1.x, w1.x, acc[2]);
+    acc[3] = zfma(h1.y, w1.y, acc[3]);
+  }
+  for (int q = nq; 2 * q < nc; ++q) {
+    const double2 h = Hv[q * hs], w = Wv[q];
+    acc[0] = zfma(h.y, w.y, zfma(h.x, w.x, acc[0]));
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// One slot row's operator entries held in registers: NV full 16-byte vectors (zero beyond the
+// row's own) and the tail vector.  Same order of the products as cluster_row_dot.
+template <int NV>
+struct RowRegs {
+  float4 h[NV], tail;
+  __device__ void load(const float* Hg, int nc) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const bool on = 4 * q + 3 < nc;
+      h[q].x = on ? Hg[(long)(4 * q) * nc] : 0.f;
+      h[q].y = on ? Hg[(long)(4 * q + 1) * nc] : 0.f;
+      h[q].z = on ? Hg[(long)(4 * q + 2) * nc] : 0.f;
+      h[q].w = on ? Hg[(long)(4 * q + 3) * nc] : 0.f;
+    }
+    const int c = nc & ~3;
+    tail.x = c < nc ? Hg[(long)c * nc] : 0.f;
+    tail.y = c + 1 < nc ? Hg[(long)(c + 1) * nc] : 0.f;
+    tail.z = c + 2 < nc ? Hg[(long)(c + 2) * nc] : 0.f;
+    tail.w = 0.f;
+  }
+  // w: the subsystem's padded vectors; nw: how many there are (at least one).  Vectors beyond
+  // them are read again from the first (their H is zero).
+  __device__ float dot(const float4* w, int nq, int ntail) const {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 wv[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) wv[q] = w[q < nq ? q : 0];
+    const float4 wt = w[ntail];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      acc[0] = zfma(h[q].x, wv[q].x, acc[0]);
+      acc[1] = zfma(h[q].y, wv[q].y, acc[1]);
+      acc[2] = zfma(h[q].z, wv[q].z, acc[2]);
+      acc[3] = zfma(h[q].w, wv[q].w, acc[3]);
+    }
+    acc[0] = zfma(tail.z, wt.z, zfma(tail.y, wt.y, zfma(tail.x, wt.x, acc[0])));
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  }
+};
+
+// The kernel's arguments, read again from the kernel-argument segment: what is only needed
+// after (or rarely in) the iteration is not held in scalar registers across it.
+template <typename A>
+__device__ __attribute__((always_inline)) inline const A& args_again() {
+  uint64_t v = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(v));
+  return *reinterpret_cast<const A*>(v);
+}
+
+// z-update of one interface of D rows at most from its members' y (Eq. 16-21).
+template <typename T, int D>
+__device__ inline void cluster_z(const T* ev, const T* ya, const T* yb, T ib0, T ib1, T iws, T mu, T ksj, T asj, int kind,
+                                 int model, T* lam) {
+  if (kind == KIND_SOFT) {
+#pragma unroll
+    for (int k = 0; k < D; ++k) lam[k] = zsoft(ev[k], ya[k], ib0, yb[k], ib1, ksj, asj);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < D; ++k) lam[k] = -zsum(ev[k], ya[k], ib0, yb[k], ib1) * iws;
+  if (kind == KIND_CONTACT) {
+    const T p3[3] = {lam[0], lam[1], lam[2]};
+    contact_project<T>(p3, mu, lam, model);
+  } else if (kind == KIND_HARD_INEQ) {
+#pragma unroll
+    for (int k = 0; k < D; ++k) lam[k] = lam[k] > (T)0 ? lam[k] : (T)0;
+  }
+}
+
+// NV > 0 (FP32, one slot row per thread, rows of at most 4 NV + 3 columns): the operator rows
+// in registers; NV = 0: in LDS.
+template <typename T, int NV>
+__global__ void __launch_bounds__(kClusterThreads) cluster_scene_kernel(ClusterArgs<T> a) {
+  using VT = typename Vec16<T>::type;
+  using X = Tagged<T>;
+  constexpr int V = Vec16<T>::N;
+  constexpr int kRows = NV > 0 ? 1 : kClusterRows / kClusterThreads;  // slot rows per thread
+  constexpr int kWaves = kClusterThreads / 64;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ __align__(16) double red[2][kWaves];
+  __shared__ __align__(16) double pred[2][kWaves];
+  __shared__ int s_lost;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  const int wg = a.order[blockIdx.x];
+  const int32_t* dsc = a.wg + 8 * (long)wg;
+  const int sc = dsc[0], sb = dsc[1], se = dsc[2], first = dsc[5], count = dsc[6], own = dsc[7];
+  const int s0 = a.g.l.t.sub_slot[sb], ns = a.g.l.t.sub_slot[se] - s0;
+  const int hq0 = a.g.l.t.sub_hq[sb], wq0 = a.g.l.t.sub_wq[sb];
+  const int lastq = (a.g.l.t.sub_nc[se - 1] + V - 1) / V;
+  const int nhq = NV > 0 ? 0 : a.g.l.t.sub_hq[se - 1] - hq0 + lastq * a.g.l.t.sub_nc[se - 1];
+  // one vector more than the padded blocks: an absent tail vector's address
+  const int nwq = a.g.l.t.sub_wq[se - 1] - wq0 + (lastq + 1) * V;
+  VT* Hq = reinterpret_cast<VT*>(smem_raw);
+  T* w = reinterpret_cast<T*>(Hq + nhq);
+  T* y = w + nwq;
+  T* u = y + ns;
+  const uint32_t tag0 = *a.epoch;
+
+  for (int q = tid; q < nwq; q += kClusterThreads) w[q] = (T)0;
+  if (tid == 0) s_lost = 0;
+  if (tid < 2 * kWaves) red[tid / kWaves][tid % kWaves] = 0.0;
+  __syncthreads();
+  int nc[kRows], hoff[kRows], wo[kRows];
+  long bx[kRows];
+  T be[kRows], dr[kRows];
+  RowRegs<(NV > 0 ? NV : 1)> hr;
+#pragma unroll
+  for (int p = 0; p < kRows; ++p) {
+    const LoopArgs<T>& l = a.g.l;
+    const int r = tid + p * kClusterThreads;
+    nc[p] = hoff[p] = wo[p] = 0;
+    bx[p] = -1;
+    be[p] = (T)1;
+    dr[p] = (T)0;
+    if (r < ns) {
+      const int g = s0 + r;
+      const int i = l.t.slot_sub[g], loc = l.t.slot_loc[g];
+      nc[p] = l.t.sub_nc[i];
+      hoff[p] = l.t.sub_hq[i] - hq0 + loc;
+      wo[p] = l.t.sub_wq[i] - wq0;
+      be[p] = l.beta[i];
+      dr[p] = l.d[g];
+      if (a.bidx[g] >= 0) bx[p] = (long)a.bidx[g] * X::N;
+      const T* Hg = l.H + l.t.sub_H[i] + loc;
+      if constexpr (NV > 0) {
+        hr.load(Hg, nc[p]);
+      } else {
+        for (int cb = 0; cb * V < nc[p]; ++cb) {
+          T v[V];
+#pragma unroll
+          for (int k = 0; k < V; ++k) v[k] = cb * V + k < nc[p] ? Hg[(long)(cb * V + k) * nc[p]] : (T)0;
+          Hq[hoff[p] + cb * nc[p]] = Vec16<T>::make(v);
+        }
+      }
+      const T z0 = l.z_in ? l.z_in[g] : (T)0;
+      const T u0 = l.u_in ? l.u_in[g] : (T)0;
+      const T wi = be[p] * z0 - u0, yi = be[p] * z0 + u0;
+      w[wo[p] + loc] = wi;
+      y[r] = yi;
+      u[r] = u0;
+      a.g.w[g] = wi;  // start values, for the tail kernel
+      a.g.y[g] = yi;
+      a.g.u[g] = u0;
+    }
+  }
+  // this thread's interface: local slots pa, pb (-1: the other workgroup's, read from the
+  // exchange buffer at xo)
+  const int f = dsc[3] + tid;
+  const bool has_if = f < dsc[4];
+  int kind = -1, dim = 0, pa = -1, pb = -1, qa = 0, qb = 0;
+  long xo = -1;
+  bool xa = false, two = false;
+  T ib0 = (T)0, ib1 = (T)0, iws = (T)0, mu = (T)0, ksj = (T)0, asj = (T)0;
+  T ev[kMaxIfDim];
+#pragma unroll
+  for (int k = 0; k < kMaxIfDim; ++k) ev[k] = (T)0;
+  if (has_if) {
+    const LoopArgs<T>& l = a.g.l;
+    const int j = a.if_list[f];
+    kind = l.t.if_kind[j];
+    dim = l.t.if_dim[j];
+    two = l.t.if_nsub[j] == 2;
+    const int sa = l.t.if_sub0[j], sbb = two ? l.t.if_sub1[j] : sa;
+    ib0 = (T)1 / l.beta[sa];
+    ib1 = two ? (T)1 / l.beta[sbb] : (T)0;
+    iws = (T)1 / (ib0 + ib1);
+    mu = l.mu[j];
+    ksj = l.ksoft[j];
+    asj = l.asoft[j];
+    const int erow = l.t.if_row[j];
+#pragma unroll
+    for (int k = 0; k < kMaxIfDim; ++k)
+      if (k < dim) ev[k] = l.e[erow + k];
+    const int g0 = l.t.if_slot0[j];
+    if (sa >= sb && sa < se) {
+      pa = g0 - s0;
+      qa = l.t.sub_wq[sa] - wq0 + (g0 - l.t.sub_slot[sa]);
+    } else {
+      xo = (long)a.bidx[g0] * X::N;
+      xa = true;
+    }
+    if (two) {
+      const int g1 = l.t.if_slot1[j];
+      if (sbb >= sb && sbb < se) {
+        pb = g1 - s0;
+        qb = l.t.sub_wq[sbb] - wq0 + (g1 - l.t.sub_slot[sbb]);
+      } else {
+        xo = (long)a.bidx[g1] * X::N;
+      }
+    }
+  }
+  // addresses for the loads of absent rows and members (their values are not used)
+  const int la = pa >= 0 ? pa : 0, lb = pb >= 0 ? pb : 0;
+  const int big = __any(dim > 3) ? 1 : 0;  // this wave holds interfaces of more than three rows
+  const int npw = (count + 63) / 64;       // waves that read the scene's partials
+  const int max_iters = a.g.l.max_iters, model = a.g.l.contact_model;
+  const double tol2 = a.g.l.tol * a.g.l.tol;
+  const long y_par = a.n_ex * X::N, p_par = (long)a.n_wg * 4;
+  unsigned long long* const ybuf = a.ybuf;
+  unsigned long long* const part = a.part + 4 * (long)first;
+  __syncthreads();
+
+  int it = 0, conv = 0;
+  double th = 0.0, yy = 0.0;
+  bool lost = false;
+  for (int li = 0; li < max_iters; ++li) {
+    it = li + 1;
+    const uint32_t tag = tag0 + (uint32_t)it;
+    unsigned long long* yb = ybuf + (li & 1 ? y_par : 0);
+    unsigned long long* pt = part + (li & 1 ? p_par : 0);
+    // x-update (Eq. 15 reassociated), y = beta x + u (Eq. 18), published where another
+    // workgroup's interface reads it
+    double pth = 0.0, pyy = 0.0;
+#pragma unroll
+    for (int p = 0; p < kRows; ++p) {
+      const int r = tid + p * kClusterThreads;
+      if (r < ns) {
+        const T yo = y[r], uo = u[r];
+        T x;
+        if constexpr (NV > 0)
+          x = hr.dot(reinterpret_cast<const VT*>(w + wo[p]), nc[p] >> 2, nc[p] >> 2);
+        else
+          x = cluster_row_dot(Hq + hoff[p], reinterpret_cast<const VT*>(w + wo[p]), nc[p], nc[p]);
+        const T yn = be[p] * (dr[p] + x) + uo;
+        if (bx[p] >= 0) X::put(yb + bx[p], yn, tag);
+        const double df = (double)yn - (double)yo;
+        pth = df * df + pth;
+        pyy = (double)yn * (double)yn + pyy;
+        y[r] = yn;
+      }
+    }
+    if (wv * 64 < ns) {
+      pth = wave_total_lane63(pth);
+      pyy = wave_total_lane63(pyy);
+      if (lane == 63) {
+        red[0][wv] = pth;
+        red[1][wv] = pyy;
+      }
+    }
     __syncthreads();
-    if (large_residual_scene<T>(a, sc, it, red, &stop)) break;
-    for (int j = i0 + tid; j < i1; j += bd) large_zupdate_if<T>(a, j);
+    // the workgroup's partials (waves in a fixed order), published by the first two threads
+    double sth = 0.0, syy = 0.0;
+    if (tid < 2) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) s += red[tid][q];
+      Tagged<double>::put(pt + 4 * own + 2 * tid, s, tag);
+    }
+    // the local members' y, then the waits: the scene's partials (one thread per workgroup of
+    // the scene) and the other workgroup's y of this thread's interface, all loads of a poll
+    // in flight together
+    T ya[kMaxIfDim], yc[kMaxIfDim], yr[kMaxIfDim];
+    auto stage = [&](auto dc) {
+      constexpr int D = decltype(dc)::value;
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        const int kk = k < dim ? k : 0;
+        ya[k] = y[la + kk];
+        yc[k] = y[lb + kk];
+        yr[k] = (T)0;
+      }
+      bool pw = tid < count, yw = xo >= 0;
+      const unsigned long long* py = yb + (yw ? xo : 0);
+      const unsigned long long* pp = pt + 4 * (pw ? tid : 0);
+      long long t0 = 0;
+      for (unsigned n = 0; pw || yw;) {
+        double p0, p1;
+        bool okp = Tagged<double>::get(pp, &p0, tag);
+        okp = Tagged<double>::get(pp + 2, &p1, tag) & okp;
+        T v[D];
+        bool oky = true;
+        if (yw) {
+#pragma unroll
+          for (int k = 0; k < D; ++k) oky = X::get(py + (k < dim ? k : 0) * X::N, &v[k], tag) & oky;
+          if (oky) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) yr[k] = v[k];
+            yw = false;
+          }
+        }
+        if (pw && okp) {
+          sth = p0;
+          syy = p1;
+          pw = false;
+        }
+        if (pw || yw) {
+          const ClusterArgs<T>& b = args_again<ClusterArgs<T>>();
+          if ((++n & 63) == 0 || b.wait_ticks == 0) {
+            const long long now = wall_clock64();
+            if (t0 == 0) t0 = now;
+            if (now - t0 >= b.wait_ticks ||
+                __hip_atomic_load(b.lost + sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+              s_lost = 1;
+              break;
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        ya[k] = xa ? yr[k] : ya[k];
+        yc[k] = !two ? (T)0 : pb >= 0 ? yc[k] : yr[k];
+      }
+    };
+    if (big)
+      stage(std::integral_constant<int, kMaxIfDim>{});
+    else
+      stage(std::integral_constant<int, 3>{});
+    if (wv < npw) {
+      sth = wave_total_lane63(sth);
+      syy = wave_total_lane63(syy);
+      if (lane == 63) {
+        pred[0][wv] = sth;
+        pred[1][wv] = syy;
+      }
+    }
+    __syncthreads();
+    // the test of Eq. 22, from the same sums in every workgroup of the scene
+    th = pred[0][0];
+    yy = pred[1][0];
+    for (int q = 1; q < npw; ++q) {
+      th += pred[0][q];
+      yy += pred[1][q];
+    }
+    if (s_lost) {
+      lost = true;
+      break;
+    }
+    if (!__builtin_isfinite(th) || !__builtin_isfinite(yy)) {
+      if (tid == 0) atomicOr(args_again<ClusterArgs<T>>().g.l.flags, FLAG_NONFINITE);
+      break;
+    }
+    if (th <= tol2 * (yy > 1e-24 ? yy : 1e-24)) {
+      conv = 1;
+      break;
+    }
+    if (it == max_iters) break;
+    // z-update (Eq. 16-21) and dual update (Eq. 14)
+    auto update = [&](auto dc) {
+      constexpr int D = decltype(dc)::value;
+      T lam[D];
+      cluster_z<T, D>(ev, ya, yc, ib0, ib1, iws, mu, ksj, asj, kind, model, lam);
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        if (k < dim) {
+          if (pa >= 0) {
+            u[pa + k] = -lam[k];
+            w[qa + k] = ya[k] + (T)2 * lam[k];
+          }
+          if (pb >= 0) {
+            u[pb + k] = -lam[k];
+            w[qb + k] = yc[k] + (T)2 * lam[k];
+          }
+        }
+      }
+    };
+    if (has_if) {
+      if (big)
+        update(std::integral_constant<int, kMaxIfDim>{});
+      else
+        update(std::integral_constant<int, 3>{});
+    }
     __syncthreads();
   }
-  for (int g = d0 + tid; g < d1; g += bd) large_final_item<T>(a, g, true, false, false);
-  for (int g = s0 + tid; g < s1; g += bd) large_final_item<T>(a, g, false, true, false);
-  for (int j = i0 + tid; j < i1; j += bd) large_final_item<T>(a, j, false, false, true);
+  const ClusterArgs<T>& b = args_again<ClusterArgs<T>>();
+  const LoopArgs<T>& l = b.g.l;
+  if (lost) {
+    if (tid == 0) __hip_atomic_store(b.lost + sc, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  // v_hat = c + G w, z, u, lambda = -u of this workgroup's subsystems
+  if (l.v_hat) {
+    const int d0 = l.t.sub_dof[sb], d1 = l.t.sub_dof[se];
+    for (int dg = d0 + tid; dg < d1; dg += kClusterThreads) {
+      int i = sb;
+      while (i + 1 < se && l.t.sub_dof[i + 1] <= dg) ++i;
+      const int n = l.t.sub_n[i], nci = l.t.sub_nc[i];
+      const T* G = l.G + l.t.sub_J[i] + (dg - l.t.sub_dof[i]);
+      const T* wi = w + (l.t.sub_wq[i] - wq0);
+      T v = l.cvec[dg];
+      for (int c = 0; c < nci; ++c) v += G[(long)c * n] * wi[c];
+      l.v_hat[dg] = v;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < kRows; ++p) {
+    const int r = tid + p * kClusterThreads;
+    if (r < ns) {
+      l.z_out[s0 + r] = (w[wo[p] + l.t.slot_loc[s0 + r]] + u[r]) / be[p];
+      l.u_out[s0 + r] = u[r];
+    }
+  }
+  if (has_if && pa >= 0 && l.lambda) {
+    const int erow = l.t.if_row[b.if_list[f]];
+    for (int k = 0; k < dim; ++k) l.lambda[erow + k] = -u[pa + k];
+  }
+  if (tid == 0 && wg == first) {
+    const double yn = __builtin_sqrt(yy);
+    l.st_iters[sc] = it;
+    l.st_conv[sc] = conv;
+    l.st_theta[sc] = th;
+    l.st_rtheta[sc] = __builtin_sqrt(th) / (yn > 1e-12 ? yn : 1e-12);
+  }
 }
+
+// After the cluster kernel, one workgroup per scene: the totals of a scene that ran through,
+// or the whole iteration of one whose waits expired; then the tags of the next launch.
+template <typename T>
+__global__ void __launch_bounds__(1024) cluster_tail_kernel(ClusterArgs<T> a) {
+  __shared__ double red[2][4];
+  __shared__ int stop;
+  const int sc = blockIdx.x;
+  if (sc == 0 && threadIdx.x == 0) *a.epoch += (uint32_t)a.g.l.max_iters + 1u;
+  if (a.lost[sc]) {
+    __syncthreads();
+    if (threadIdx.x == 0) a.lost[sc] = 0;
+    large_scene_iterate<T>(a.g, sc, red, &stop);
+  } else if (threadIdx.x == 0) {
+    a.g.l.st_total[sc] += a.g.l.st_iters[sc];
+    if (!a.g.l.st_conv[sc]) a.g.l.st_unconv[sc] += 1;
+  }
+}
+
+// The form for rows of at most max_nc columns and `rows` slot rows per workgroup.
+template <typename T, typename F>
+hipError_t cluster_form(int max_nc, int rows, F&& f) {
+  if constexpr (sizeof(T) == sizeof(float)) {
+    if (rows <= kClusterThreads) {
+      if (max_nc <= 24 + 3) return f(std::integral_constant<int, 6>{});
+      if (max_nc <= 48 + 3) return f(std::integral_constant<int, 12>{});
+      if (max_nc <= 72 + 3) return f(std::integral_constant<int, 18>{});
+    }
+  }
+  return f(std::integral_constant<int, 0>{});
+}
+
+// Workgroups the device holds at once with `lds` bytes of dynamic LDS each.
+template <typename T>
+hipError_t cluster_capacity(const ClusterShape& c, int* wgs) {
+  *wgs = 0;
+  return cluster_form<T>(c.max_nc, c.rows, [&](auto nv) -> hipError_t {
+    constexpr int NV = decltype(nv)::value;
+    const size_t lds = NV > 0 ? c.lds_w : c.lds;
+    const void* fn = reinterpret_cast<const void*>(&cluster_scene_kernel<T, NV>);
+    int dev = 0, cus = 0, per = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kClusterThreads, lds);
+    if (e == hipSuccess) *wgs = per * cus;
+    return e;
+  });
+}
+template hipError_t cluster_capacity<float>(const ClusterShape&, int*);
+template hipError_t cluster_capacity<double>(const ClusterShape&, int*);
+
+template <typename T>
+hipError_t launch_cluster(const ClusterArgs<T>& a, const ClusterShape& c, int tail_threads, hipStream_t s) {
+  if (a.g.l.t.n_scene == 0 || a.n_wg == 0) return hipSuccess;
+  const hipError_t e = cluster_form<T>(c.max_nc, c.rows, [&](auto nv) -> hipError_t {
+    constexpr int NV = decltype(nv)::value;
+    hipLaunchKernelGGL((cluster_scene_kernel<T, NV>), dim3(a.n_wg), dim3(kClusterThreads), NV > 0 ? c.lds_w : c.lds, s, a);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(cluster_tail_kernel<T>, dim3(a.g.l.t.n_scene), dim3(tail_threads), 0, s, a);
+  return hipGetLastError();
+}
+template hipError_t launch_cluster<float>(const ClusterArgs<float>&, const ClusterShape&, int, hipStream_t);
+template hipError_t launch_cluster<double>(const ClusterArgs<double>&, const ClusterShape&, int, hipStream_t);
 
 __global__ void __launch_bounds__(256) large_alldone_kernel(const int32_t* done, int n_scene, int32_t* all_done) {
   __shared__ int open;

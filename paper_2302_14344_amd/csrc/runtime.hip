@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -33,6 +34,13 @@ constexpr int kLargePoll = 32;
 // thread; beyond that one phase of one scene is better spread over the GPU (a 320-segment
 // cable of ~3.4k rows took 47 us per iteration in one workgroup, 13 us in the phase form)
 constexpr int kLargeSceneMax = 2048;
+// several workgroups per large scene: slot rows a workgroup aims at (64 to 384 measured within
+// 10%: cable 295-265 us, stir 327-305 us, mixed batch 388 us per step at any of them; few rows
+// make more workgroups exchange, many lengthen the x-update), workgroups in all (one per CU),
+// and how long a workgroup waits for another before the scene is run again by the tail kernel
+// (20 ms of the 100 MHz clock)
+constexpr int kClusterTarget = 256, kClusterWgs = 256;
+constexpr long long kClusterWait = 2000000;
 
 struct Plan {
   size_t off = 0;
@@ -134,6 +142,13 @@ struct subadmm_problem {
   bool sub_ok = true;
   std::string sub_why;
   int32_t force_large = 0;  // option SUBADMM_OPT_LARGE_PATH
+  // large scenes cut into several workgroups each (empty: not usable for this problem):
+  // per workgroup 8 entries, dispatch order, interface lists, exchanged slot rows
+  std::vector<int32_t> cl_wg, cl_order, cl_if, cl_bidx;
+  int64_t cl_nex = 0;
+  subadmm::ClusterShape cl_shape;
+  bool cl_fits = false;     // the bound device holds every workgroup at once
+  long long cl_wait = kClusterWait;
   int32_t boyd = 0;         // option SUBADMM_OPT_BOYD_RESIDUALS
   bool boyd_valid = false;  // the last solve or step wrote r_prim and r_dual
 
@@ -170,7 +185,9 @@ struct subadmm_problem {
         f_dkey_off, f_perm, f_jtj, f_slot_dk, f_slot_dof, f_dk_off, f_dk_slot, f_if_node0, f_if_node1, f_slot_sgn,
         f_tet_g, f_tet_vol, f_rest, f_mass, f_lame_l, f_lame_m, f_sq_off;
     size_t fA, fb, fL, fS, fcd, fscr, fe, fvh, fw, fy, fpart, fprec, fkest;
+    size_t cl_wg, cl_order, cl_if, cl_bidx, cl_y, cl_part, cl_lost, cl_epoch;
     size_t static_end;
+    size_t base;   // end of what every entry point needs (subadmm_solve_scratch holds this much)
     size_t total;
   } o{};
   std::vector<char> upload_keep;  // host staging kept alive until bind's synchronisation
@@ -421,7 +438,105 @@ void plan_workspace(subadmm_problem* p) {
     o.fprec = pl.take<int32_t>(p->n_sub);
     o.fkest = pl.take<double>(p->n_sub);
   }
+  o.base = (pl.off + 255) & ~size_t(255);
+  pl.off = o.base;
+  if (!p->cl_wg.empty() && !p->has_fem) {
+    const size_t words = p->dtype == SUBADMM_F64 ? kClusterWordsF64 : kClusterWordsF32;
+    o.cl_wg = pl.take<int32_t>(p->cl_wg.size());
+    o.cl_order = pl.take<int32_t>(p->cl_order.size());
+    o.cl_if = pl.take<int32_t>(p->cl_if.size());
+    o.cl_bidx = pl.take<int32_t>(p->cl_bidx.size());
+    o.cl_y = pl.take<unsigned long long>(2 * words * (size_t)p->cl_nex);
+    o.cl_part = pl.take<unsigned long long>(p->cl_wg.size());  // 2 x 4 words per workgroup
+    o.cl_lost = pl.take<int32_t>(p->n_scene);
+    o.cl_epoch = pl.take<uint32_t>(1);
+  }
   o.total = (pl.off + 255) & ~size_t(255);
+}
+
+// Cuts every scene into runs of consecutive subsystems, one workgroup each, of about equal
+// slot rows: kClusterTarget rows each unless that takes more than kClusterWgs workgroups in
+// all (one per CU).  Left empty where an interface has more than two members, or a
+// run does not fit a workgroup (LDS, rows, interfaces).
+void plan_cluster(subadmm_problem* p) {
+  p->cl_wg.clear();
+  p->cl_order.clear();
+  p->cl_if.clear();
+  p->cl_bidx.clear();
+  p->cl_nex = 0;
+  p->cl_shape = ClusterShape{};
+  if (p->small_ok || !p->sub_ok || p->max_members > 2 || p->n_scene > kClusterWgs) return;
+  const int32_t V = (int32_t)(16 / p->rsize());
+  std::vector<int32_t> sub_wg(p->n_sub, -1);
+  std::vector<std::array<int32_t, 8>> wgs;
+  auto lds_of = [&](int64_t hq, int64_t wq, int64_t rows) {
+    return (size_t)(16 * hq) + p->rsize() * (size_t)(wq + V + 2 * rows) + 64;
+  };
+  for (int32_t s = 0; s < p->n_scene; ++s) {
+    const int32_t rows_s = p->sc_slot[s + 1] - p->sc_slot[s];
+    const int64_t W = std::max<int64_t>(1, std::min<int64_t>((rows_s + kClusterTarget - 1) / kClusterTarget,
+                                                              (int64_t)rows_s * kClusterWgs / std::max<int64_t>(p->n_slot, 1)));
+    const int32_t first = (int32_t)wgs.size();
+    int64_t hq = 0, wq = 0, rows = 0, nif = 0;
+    int32_t beg = p->sc_sub[s];
+    auto close = [&](int32_t end) {
+      if (end == beg) return;
+      wgs.push_back({s, beg, end, 0, 0, first, 0, 0});
+      for (int32_t i = beg; i < end; ++i) sub_wg[i] = (int32_t)wgs.size() - 1;
+      beg = end;
+      hq = wq = rows = nif = 0;
+    };
+    for (int32_t i = p->sc_sub[s]; i < p->sc_sub[s + 1]; ++i) {
+      const int64_t nc = p->sub_nc[i], nq = (nc + V - 1) / V;
+      int64_t ifs = 0;  // interfaces of subsystem i (an upper bound of what it adds to a run)
+      for (int64_t g = p->sub_slot[i]; g < p->sub_slot[i + 1]; ++g) ifs += (p->slot_mk[g] & 7) == 0;
+      // end the run before i when i would take it further past its share than it is short of
+      const int64_t share = (int64_t)rows_s * ((int64_t)wgs.size() - first + 1) / W;
+      const int64_t done = p->sub_slot[i] - p->sc_slot[s];
+      const bool full = rows + nc > kClusterRows || nif + ifs > kClusterThreads ||
+                        lds_of(hq + nq * nc, wq + nq * V, rows + nc) > kClusterLds;
+      if (full || (rows > 0 && done + nc - share > share - done)) close(i);
+      hq += nq * nc;
+      wq += nq * V;
+      rows += nc;
+      nif += ifs;
+      if (rows > kClusterRows || nif > kClusterThreads || lds_of(hq, wq, rows) > kClusterLds) return;
+      p->cl_shape.lds = std::max(p->cl_shape.lds, lds_of(hq, wq, rows));
+      p->cl_shape.lds_w = std::max(p->cl_shape.lds_w, lds_of(0, wq, rows));
+      p->cl_shape.rows = std::max(p->cl_shape.rows, (int)rows);
+    }
+    close(p->sc_sub[s + 1]);
+    const int32_t count = (int32_t)wgs.size() - first;
+    for (int32_t m = 0; m < count; ++m) {
+      wgs[first + m][6] = count;
+      wgs[first + m][7] = m;
+    }
+    if ((int)wgs.size() > 2 * kClusterWgs || count > kClusterThreads) return;
+  }
+  p->cl_shape.max_nc = p->max_nc;
+  // interfaces of each workgroup by kind and rows, so that a wave holds few classes
+  std::vector<std::vector<std::pair<int32_t, int32_t>>> lists(wgs.size());
+  p->cl_bidx.assign(p->n_slot, -1);
+  for (int32_t j = 0; j < p->n_if; ++j) {
+    const int32_t wa = sub_wg[p->if_sub0[j]];
+    const int32_t wb = p->if_nsub[j] == 2 ? sub_wg[p->if_sub1[j]] : wa;
+    const int32_t cls = p->if_kind[j] * 32 + p->if_dim[j] * 2 + (wa == wb);
+    lists[wa].push_back({cls, j});
+    if (wa == wb) continue;
+    lists[wb].push_back({cls, j});
+    for (int32_t k = 0; k < p->if_dim[j]; ++k) p->cl_bidx[p->if_slot0[j] + k] = (int32_t)p->cl_nex++;
+    for (int32_t k = 0; k < p->if_dim[j]; ++k) p->cl_bidx[p->if_slot1[j] + k] = (int32_t)p->cl_nex++;
+  }
+  for (size_t q = 0; q < wgs.size(); ++q) {
+    std::stable_sort(lists[q].begin(), lists[q].end(),
+                     [](const std::pair<int32_t, int32_t>& x, const std::pair<int32_t, int32_t>& y) { return x.first < y.first; });
+    wgs[q][3] = (int32_t)p->cl_if.size();
+    for (const auto& e : lists[q]) p->cl_if.push_back(e.second);
+    wgs[q][4] = (int32_t)p->cl_if.size();
+  }
+  for (const auto& w : wgs) p->cl_wg.insert(p->cl_wg.end(), w.begin(), w.end());
+  p->cl_order.resize(wgs.size());
+  for (size_t q = 0; q < wgs.size(); ++q) p->cl_order[q] = (int32_t)q;
 }
 
 template <typename X>
@@ -724,6 +839,26 @@ int run_loop(subadmm_problem* p, const T* e, int32_t max_iters, double tol, cons
     lg.all_done = at<int32_t>(p, o.lall);
     lg.n_slot = p->n_slot;
     lg.n_dof = p->n_dof;
+    // several workgroups per scene where every one of them is resident at once; the scratch
+    // entry, whose array does not hold the exchange buffers, takes the forms below
+    if (p->cl_fits && p->force_large == 0 && !p->in_scratch) {
+      ClusterArgs<T> ca;
+      ca.g = lg;
+      ca.wg = at<int32_t>(p, o.cl_wg);
+      ca.order = at<int32_t>(p, o.cl_order);
+      ca.if_list = at<int32_t>(p, o.cl_if);
+      ca.bidx = at<int32_t>(p, o.cl_bidx);
+      ca.ybuf = at<unsigned long long>(p, o.cl_y);
+      ca.part = at<unsigned long long>(p, o.cl_part);
+      ca.lost = at<int32_t>(p, o.cl_lost);
+      ca.epoch = at<uint32_t>(p, o.cl_epoch);
+      ca.wait_ticks = p->cl_wait;
+      ca.n_ex = p->cl_nex;
+      ca.n_wg = (int32_t)(p->cl_wg.size() / 8);
+      return dev_err(p, timed(p, SUBADMM_K_LOOP,
+                              [&] { return launch_cluster<T>(ca, p->cl_shape, large_threads(p), p->stream); }),
+                     "large-scene iteration");
+    }
     // eager steps stop launching once every scene has stopped (checked every 32 iterations);
     // a captured graph and the scratch entry launch every permitted iteration
     const int poll = (p->capturing || p->in_scratch) ? 0 : kLargePoll;
@@ -1023,6 +1158,7 @@ SUBADMM_API int subadmm_setup(const subadmm_subsystem* subs, int32_t n_sub, cons
   if (R * (3 * (size_t)p->max_slot_scene + (size_t)p->max_row_scene) > 150 * 1024)
     small_no("a scene's slot vectors do not fit in LDS");
   if (p->sub_ok) plan_factor(p);
+  plan_cluster(p);
   if (p->small_ok) {
     // interface map of the thread-per-interface kernel: the block size its launcher
     // chooses, and per scene one interface class (kind, dim) per wave when they fit
@@ -1577,6 +1713,16 @@ int upload_all(subadmm_problem* p) {
   hipError_t e = hipMemcpyAsync(p->ws, p->upload_keep.data(), o.static_end, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess && o.total > o.static_end)
     e = hipMemsetAsync(p->ws + o.static_end, 0, o.total - o.static_end, p->stream);
+  if (!p->cl_wg.empty() && !p->has_fem) {
+    auto put = [&](size_t off, const std::vector<int32_t>& v) {
+      if (e == hipSuccess && !v.empty())
+        e = hipMemcpyAsync(p->ws + off, v.data(), v.size() * sizeof(int32_t), hipMemcpyHostToDevice, p->stream);
+    };
+    put(o.cl_wg, p->cl_wg);
+    put(o.cl_order, p->cl_order);
+    put(o.cl_if, p->cl_if);
+    put(o.cl_bidx, p->cl_bidx);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   return dev_err(p, e, "bind upload");
 }
@@ -1618,6 +1764,14 @@ SUBADMM_API int subadmm_bind(subadmm_problem* p, void* dev_workspace, size_t byt
   int rc = upload_all(p);
   p->bound = rc == SUBADMM_OK;
   if (rc) return rc;
+  p->cl_fits = false;
+  if (!p->cl_wg.empty() && !p->has_fem) {
+    int cap = 0;
+    const hipError_t ce = p->dtype == SUBADMM_F64 ? cluster_capacity<double>(p->cl_shape, &cap)
+                                                  : cluster_capacity<float>(p->cl_shape, &cap);
+    if (ce != hipSuccess) (void)hipGetLastError();  // the other forms need no such guarantee
+    p->cl_fits = ce == hipSuccess && (size_t)cap >= p->cl_wg.size() / 8;
+  }
   release_graph(p);
   release_side(p);
   if (p->sub_ok && p->buckets.size() > 1) {
@@ -1639,6 +1793,16 @@ SUBADMM_API int subadmm_bind(subadmm_problem* p, void* dev_workspace, size_t byt
     }
   }
   return SUBADMM_OK;
+}
+
+// For tests (not in the header): sets how long (ticks of the 100 MHz clock, < 0: the default)
+// a workgroup of a large scene waits for another before it gives the scene up to the tail
+// kernel, and returns the workgroups the problem's scenes are cut into (0: not in this form).
+SUBADMM_API int subadmm_large_scene_wait(subadmm_problem* p, long long ticks) {
+  if (!p) return 0;
+  p->cl_wait = ticks < 0 ? kClusterWait : ticks;
+  ++p->cfg_gen;
+  return p->cl_fits ? (int)(p->cl_wg.size() / 8) : 0;
 }
 
 SUBADMM_API int subadmm_solve(subadmm_problem* p, const void* A, const void* b, const void* J, const void* e,
@@ -1718,8 +1882,8 @@ SUBADMM_API int subadmm_solve_scratch(subadmm_problem* p, void* hip_stream, cons
   if (warm == SUBADMM_WARM_GIVEN && (!z0 || !u0)) return fail(p, SUBADMM_E_ARG, "warm GIVEN needs z0 and u0");
   if (!A || !b || (p->n_J > 0 && !J) || (p->n_rows > 0 && !e)) return fail(p, SUBADMM_E_ARG, "null input array");
   if (!p->sub_ok) return fail(p, SUBADMM_E_ARG, "problem exceeds the per-subsystem solver: " + p->sub_why);
-  if (p->o.total > kScratchBytes)
-    return fail(p, SUBADMM_E_WORKSPACE, "problem needs " + std::to_string(p->o.total) +
+  if (p->o.base > kScratchBytes)
+    return fail(p, SUBADMM_E_WORKSPACE, "problem needs " + std::to_string(p->o.base) +
                                             " bytes of scratch; the static scratch holds " +
                                             std::to_string(kScratchBytes));
   if (p->capturing || p->timing) return fail(p, SUBADMM_E_STATE, "scratch solve during capture or timing");
@@ -1743,8 +1907,8 @@ SUBADMM_API int subadmm_solve_scratch(subadmm_problem* p, void* hip_stream, cons
   if (p->upload_keep.size() != p->o.static_end) rc = stage_tables(p);
   hipError_t he = hipSuccess;
   if (!rc) he = hipMemcpyAsync(ptr, p->upload_keep.data(), p->o.static_end, hipMemcpyHostToDevice, p->stream);
-  if (!rc && he == hipSuccess && p->o.total > p->o.static_end) {
-    const size_t n16 = (p->o.total - p->o.static_end) / 16;  // both offsets are 256-byte aligned
+  if (!rc && he == hipSuccess && p->o.base > p->o.static_end) {
+    const size_t n16 = (p->o.base - p->o.static_end) / 16;  // both offsets are 256-byte aligned
     const unsigned blocks = (unsigned)std::min<size_t>((n16 + 255) / 256, 4096);
     hipLaunchKernelGGL(scratch_zero_kernel, dim3(blocks), dim3(256), 0, p->stream,
                        reinterpret_cast<uint4*>(ptr + p->o.static_end), n16);
