@@ -34,35 +34,84 @@ struct GemmArgs {
 
 template <typename TA, typename TB>
 hipError_t launch_gemm(const GemmArgs<TA, TB>& g, int splits, hipStream_t s);
-hipError_t launch_cast_bf16(const float* x, uint16_t* y, long n, hipStream_t s);
+// y[r][c] = bf16(x[r][c] * scale[c] + shift[c]) (or bf16(x) without scale), x dense rows of
+// `width`, y rows of ldy entries
+hipError_t launch_cast_rows(const float* x, const float* scale, const float* shift, long rows, int width, uint16_t* y,
+                            int ldy, hipStream_t s);
 hipError_t launch_gather_rows(const float* src, long n_rows, int width, const int32_t* idx, int count, float* dst,
                               hipStream_t s);
-hipError_t launch_cast_affine_bf16(const float* x, const float* scale, const float* shift, int width, uint16_t* y,
-                                  long n, hipStream_t s);
 hipError_t launch_loss_grad(const float* y, const float* t, const float* wt, float* dy, long n, double* partial,
                             int max_blocks, float* loss, hipStream_t s);
 hipError_t launch_colsum(const float* a, long rows, int cols, float* partial, int splits, float* out, hipStream_t s);
 hipError_t launch_sum_partials(const float* partial, int splits, long n, float* out, hipStream_t s);
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, float lr, float b1, float b2, float eps,
-                       int step, hipStream_t s);
+// Rows of BF16 matrices (activations, their gradients) are padded with zeros to a multiple of
+// eight entries, so every 16-byte load of eight is aligned.
+inline __host__ __device__ int mlp_ld(int w) { return (w + 7) & ~7; }
+// BF16 copies of the weights.  Wide networks: rows of mlp_ld entries.  Networks in the
+// whole-network kernels: 16 x 32 tiles in the order a wave's lanes read them as an MFMA
+// operand, so that a fragment is one contiguous kilobyte: entry (n, k) of a matrix of K columns
+// sits in tile (n / 16, k / 32) at lane 16 ((k / 8) % 4) + n % 16, entry k % 8, zero padded.
+inline __host__ __device__ long mlp_tiles(int N, int K) { return (long)((N + 15) / 16) * ((K + 31) / 32); }
+inline __host__ __device__ long mlp_tile_at(int n, int k, int K) {
+  const long tile = (long)(n >> 4) * ((K + 31) / 32) + (k >> 5);
+  return tile * 512 + 8 * (16 * ((k >> 3) & 3) + (n & 15)) + (k & 7);
+}
 
-// Whole-network inference in one launch (no activations kept for a backward pass).
-constexpr int kInferMaxLayers = 8, kInferMaxWidth = 256;
-struct MlpInferArgs {
-  const float* x;        // batch x w[0] FP32
-  float* y;              // batch x w[L] FP32
+// Layer table of a network (all kernels below).
+constexpr int kMaxLayers = 16;
+struct MlpNet {
+  int L;
+  int w[kMaxLayers + 1];
+  long off_W[kMaxLayers], off_b[kMaxLayers];    // FP32 parameter layout
+  long off_Wbf[kMaxLayers], off_WT[kMaxLayers]; // BF16 copies (w[k+1] x w[k]), and transposed
+  int tiled;                                    // layout of the BF16 copies (WT: tiled only)
+  long off_act[kMaxLayers + 1];                 // rows of ld(w[k]): the input of layer k
+  long off_dz[kMaxLayers + 1];                  // k >= 1: gradient at the output of layer k - 1
+};
+
+// BF16 copies of the FP32 parameters P (both orientations); with g: one Adam step on P first.
+struct AdamArgs {
+  float *p, *m, *v;
+  const float* g;  // nullptr: only the copies
+  uint16_t *Wbf, *WT;
+  long n;
+  float lr, b1, b2, eps, c1, c2;
+};
+hipError_t launch_update(const MlpNet& net, const AdamArgs& a, hipStream_t s);
+
+// Whole-network kernels, for networks of at most kFusedLayers layers of at most kFusedWidth.
+constexpr int kFusedLayers = 8, kFusedWidth = 256;
+constexpr int kFusedRows = 32;          // batch rows of a workgroup at a time
+constexpr int kChainBlocks = 1024;      // most workgroups of the gradient chain
+constexpr int kWeightSplits = 16;       // batch splits of the weight gradients at most
+constexpr int kBiasSplits = 64;         // row chunks of the bias gradients
+struct MlpFusedArgs {
+  MlpNet net;
+  const float* x;        // batch x w[0]
   const float* scale;    // input affine (nullptr: none)
   const float* shift;
-  const uint16_t* Wbf;   // BF16 weights, layer k: w[k+1] x w[k] row-major at off_Wbf[k]
-  const float* P;        // FP32 parameters; layer k's bias at off_b[k]
+  const float* P;
+  const uint16_t* Wbf;
+  float *y, *y2;         // batch x w[L]; y2: second copy (nullptr: none)
+  uint16_t* act;         // nullptr: activations are not kept
   long batch;
-  int L;
-  int w[kInferMaxLayers + 1];
-  long off_Wbf[kInferMaxLayers];
-  long off_b[kInferMaxLayers];
-  int vec_w[kInferMaxLayers];  // 1: layer k's weight rows allow 16-byte loads (K % 8 == 0, aligned)
 };
-hipError_t launch_mlp_infer(const MlpInferArgs& a, hipStream_t s);
+hipError_t launch_fused_forward(const MlpFusedArgs& a, hipStream_t s);
+
+struct MlpBackArgs {
+  MlpNet net;
+  const float *y, *target, *wt;  // wt may be nullptr
+  const uint16_t *act, *WT;
+  float* dz;
+  float* part;           // kWeightSplits x n_params: partial weight gradients
+  float* cpart;          // kBiasSplits x n_bias: partial bias gradients
+  double* lpart;         // chain workgroups: partial losses
+  float *grad, *grad2, *loss;  // grad2, loss: optional
+  long batch, n_params;
+  int n_bias;            // sum of w[1..L]
+  int chain_blocks, splits, chunk, tiles;  // set by launch_fused_backward
+};
+hipError_t launch_fused_backward(MlpBackArgs a, hipStream_t s);
 
 }  // namespace subadmm
 

@@ -1,10 +1,13 @@
 // Host side of the warm-start network: the subadmm_mlp_* entry points of
 // include/subadmm.h.  Layout of the bound workspace (256-byte aligned sub-arrays):
 // FP32 master parameters, gradients and the two Adam moments; BF16 copies of the
-// weights; per layer the BF16 input activations of the last forward batch; the FP32
-// output; two FP32 gradient buffers; split-K and column-sum partials.
+// weights in both orientations; per layer the BF16 input activations of the last forward
+// batch; the FP32 output; the FP32 gradients at the layers' outputs (every layer's for
+// networks that run in the whole-network kernels, else two buffers in turn); partial sums.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <string>
 #include <vector>
 
@@ -16,8 +19,8 @@
 using namespace subadmm;
 
 namespace {
-constexpr int kSplits = 16;      // split-K factor of the weight gradients
-constexpr int kColSplits = 64;   // row chunks of the bias-gradient column sums
+constexpr int kSplits = kWeightSplits;   // split-K factor of the weight gradients
+constexpr int kColSplits = kBiasSplits;  // row chunks of the bias-gradient column sums
 constexpr int kLossBlocks = 1024;
 thread_local std::string g_mlp_error;
 
@@ -28,9 +31,11 @@ struct subadmm_mlp {
   int32_t L = 0, max_batch = 0, max_w = 0;
   std::vector<int32_t> w;          // widths
   std::vector<int64_t> off_W, off_b, off_Wbf, off_act;  // element offsets
-  int64_t P = 0, n_wbf = 0, n_act = 0, max_wk = 0;
+  MlpNet net{};                    // the same for the kernels
+  bool fused = false;              // the whole-network kernels take this network
+  int64_t P = 0, n_wbf = 0, n_wt = 0, n_act = 0, n_dz = 0, n_bias = 0, max_wk = 0;
   struct {
-    size_t P, G, M, V, Wbf, act, y, dz0, dz1, part, cpart, lpart, aff, total;
+    size_t P, G, M, V, Wbf, WT, act, y, dz, dz0, dz1, part, cpart, lpart, aff, total;
   } o{};
   char* ws = nullptr;
   hipStream_t stream = nullptr;
@@ -77,7 +82,11 @@ SUBADMM_API int subadmm_mlp_create(int32_t n_layers, const int32_t* widths, int3
     m->w.push_back(widths[k]);
     m->max_w = std::max(m->max_w, widths[k]);
   }
-  int64_t p = 0, wb = 0, ac = 0;
+  int64_t p = 0, wb = 0, wt = 0, ac = 0, dz = 0;
+  m->fused = n_layers <= kFusedLayers && m->max_w <= kFusedWidth;
+  m->net.L = n_layers;
+  m->net.tiled = m->fused ? 1 : 0;
+  m->net.w[0] = m->w[0];
   for (int32_t k = 0; k < n_layers; ++k) {
     const int64_t nk = m->w[k + 1], kk = m->w[k];
     m->off_W.push_back(p);
@@ -85,14 +94,26 @@ SUBADMM_API int subadmm_mlp_create(int32_t n_layers, const int32_t* widths, int3
     m->off_b.push_back(p);
     p += nk;
     m->off_Wbf.push_back(wb);
-    wb += nk * kk;
     m->off_act.push_back(ac);
-    ac += (int64_t)max_batch * kk;
+    m->net.w[k + 1] = (int)nk;
+    m->net.off_W[k] = m->off_W[k];
+    m->net.off_b[k] = m->off_b[k];
+    m->net.off_Wbf[k] = wb;
+    m->net.off_WT[k] = wt;
+    m->net.off_act[k] = ac;
+    m->net.off_dz[k + 1] = dz;
+    wb += m->fused ? 512 * mlp_tiles((int)nk, (int)kk) : nk * mlp_ld((int)kk);
+    wt += m->fused ? 512 * mlp_tiles((int)kk, (int)nk) : 0;
+    ac += (int64_t)max_batch * mlp_ld((int)kk);
+    dz += (int64_t)max_batch * mlp_ld((int)nk);
+    m->n_bias += nk;
     m->max_wk = std::max(m->max_wk, nk * kk);
   }
   m->P = p;
   m->n_wbf = wb;
+  m->n_wt = wt;
   m->n_act = ac;
+  m->n_dz = dz;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -105,12 +126,19 @@ SUBADMM_API int subadmm_mlp_create(int32_t n_layers, const int32_t* widths, int3
   m->o.M = take(fb * m->P);
   m->o.V = take(fb * m->P);
   m->o.Wbf = take(2 * (size_t)m->n_wbf);
+  m->o.WT = take(2 * (size_t)m->n_wt);
   m->o.act = take(2 * (size_t)m->n_act);
   m->o.y = take(fb * (size_t)max_batch * m->w[n_layers]);
-  m->o.dz0 = take(fb * (size_t)max_batch * m->max_w);
-  m->o.dz1 = take(fb * (size_t)max_batch * m->max_w);
-  m->o.part = take(fb * (size_t)kSplits * m->max_wk);
-  m->o.cpart = take(fb * (size_t)kColSplits * m->max_w);
+  if (m->fused) {
+    m->o.dz = take(fb * (size_t)m->n_dz);
+    m->o.part = take(fb * (size_t)kSplits * m->P);
+    m->o.cpart = take(fb * (size_t)kColSplits * (size_t)m->n_bias);
+  } else {
+    m->o.dz0 = take(fb * (size_t)max_batch * m->max_w);
+    m->o.dz1 = take(fb * (size_t)max_batch * m->max_w);
+    m->o.part = take(fb * (size_t)kSplits * m->max_wk);
+    m->o.cpart = take(fb * (size_t)kColSplits * m->max_w);
+  }
   m->o.lpart = take(sizeof(double) * kLossBlocks);
   m->o.aff = take(fb * 2 * (size_t)m->w[0]);
   m->o.total = off;
@@ -137,14 +165,30 @@ SUBADMM_API int subadmm_mlp_bind(subadmm_mlp* m, void* dev_workspace, size_t byt
 
 namespace {
 
-int refresh_bf16(subadmm_mlp* m) {
-  for (int32_t k = 0; k < m->L; ++k) {
-    const int rc = mdev(m, launch_cast_bf16(mat<float>(m, m->o.P) + m->off_W[k], mat<uint16_t>(m, m->o.Wbf) + m->off_Wbf[k],
-                                            (long)m->w[k + 1] * m->w[k], m->stream),
-                        "cast weights");
-    if (rc) return rc;
+// The weights' BF16 copies, after an Adam step on the parameters when g is set.
+int update_params(subadmm_mlp* m, AdamArgs a, const char* where) {
+  a.p = mat<float>(m, m->o.P);
+  a.m = mat<float>(m, m->o.M);
+  a.v = mat<float>(m, m->o.V);
+  a.Wbf = mat<uint16_t>(m, m->o.Wbf);
+  a.WT = mat<uint16_t>(m, m->o.WT);
+  a.n = (long)m->P;
+  return mdev(m, launch_update(m->net, a, m->stream), where);
+}
+
+// Inputs and weights of the whole-network forward pass.
+MlpFusedArgs fused_args(subadmm_mlp* m, int32_t batch, const float* x) {
+  MlpFusedArgs a{};
+  a.net = m->net;
+  a.x = x;
+  if (m->affine) {
+    a.scale = mat<float>(m, m->o.aff);
+    a.shift = a.scale + m->w[0];
   }
-  return SUBADMM_OK;
+  a.P = mat<float>(m, m->o.P);
+  a.Wbf = mat<uint16_t>(m, m->o.Wbf);
+  a.batch = batch;
+  return a;
 }
 
 int check_bound(subadmm_mlp* m) {
@@ -164,7 +208,7 @@ SUBADMM_API int subadmm_mlp_set_params(subadmm_mlp* m, const float* params) {
   if (e == hipSuccess) e = hipMemsetAsync(m->ws + m->o.V, 0, sizeof(float) * m->P, m->stream);
   rc = mdev(m, e, "set params");
   if (rc) return rc;
-  return refresh_bf16(m);
+  return update_params(m, AdamArgs{}, "cast weights");
 }
 
 SUBADMM_API int subadmm_mlp_set_input_affine(subadmm_mlp* m, const float* scale, const float* shift) {
@@ -200,28 +244,31 @@ SUBADMM_API int subadmm_mlp_forward(subadmm_mlp* m, int32_t batch, const float* 
   if (!x || !y) return mfail(m, SUBADMM_E_ARG, "null input/output");
   m->last_batch = batch;
   if (batch == 0) return SUBADMM_OK;
+  float* ybuf = mat<float>(m, m->o.y);
+  if (m->fused) {
+    MlpFusedArgs a = fused_args(m, batch, x);
+    a.act = mat<uint16_t>(m, m->o.act);
+    a.y = ybuf;
+    a.y2 = y;
+    return mdev(m, launch_fused_forward(a, m->stream), "forward");
+  }
   uint16_t* act = mat<uint16_t>(m, m->o.act);
   const uint16_t* Wb = mat<uint16_t>(m, m->o.Wbf);
   const float* P = mat<float>(m, m->o.P);
-  float* ybuf = mat<float>(m, m->o.y);
-  if (m->affine) {
-    const float* aff = mat<float>(m, m->o.aff);
-    rc = mdev(m, launch_cast_affine_bf16(x, aff, aff + m->w[0], m->w[0], act + m->off_act[0], (long)batch * m->w[0],
-                                         m->stream),
-              "normalise input");
-  } else {
-    rc = mdev(m, launch_cast_bf16(x, act + m->off_act[0], (long)batch * m->w[0], m->stream), "cast input");
-  }
+  const float* aff = m->affine ? mat<float>(m, m->o.aff) : nullptr;
+  rc = mdev(m, launch_cast_rows(x, aff, aff ? aff + m->w[0] : nullptr, batch, m->w[0], act + m->off_act[0],
+                                mlp_ld(m->w[0]), m->stream),
+            "cast input");
   if (rc) return rc;
   for (int32_t k = 0; k < m->L; ++k) {
     const long N = m->w[k + 1], K = m->w[k];
     GemmArgs<uint16_t, uint16_t> g{};
     g.A = act + m->off_act[k];
-    g.sam = K;
+    g.sam = mlp_ld((int)K);
     g.sak = 1;
     g.B = Wb + m->off_Wbf[k];
     g.sbk = 1;
-    g.sbn = K;
+    g.sbn = mlp_ld((int)K);
     g.M = batch;
     g.N = N;
     g.K = K;
@@ -232,7 +279,7 @@ SUBADMM_API int subadmm_mlp_forward(subadmm_mlp* m, int32_t batch, const float* 
     if (k + 1 < m->L) {
       g.epi = EPI_BIAS_RELU_BF16;
       g.out_bf16 = act + m->off_act[k + 1];
-      g.ldo = N;
+      g.ldo = mlp_ld((int)N);
     } else {
       g.epi = EPI_BIAS_F32;
       g.C = ybuf;
@@ -255,6 +302,25 @@ SUBADMM_API int subadmm_mlp_backward(subadmm_mlp* m, int32_t batch, const float*
   if (batch == 0) {
     rc = mdev(m, hipMemsetAsync(G, 0, sizeof(float) * m->P, m->stream), "clear grad");
     if (rc) return rc;
+  } else if (m->fused) {
+    MlpBackArgs a{};
+    a.net = m->net;
+    a.y = mat<float>(m, m->o.y);
+    a.target = target;
+    a.wt = wt;
+    a.act = mat<uint16_t>(m, m->o.act);
+    a.WT = mat<uint16_t>(m, m->o.WT);
+    a.dz = mat<float>(m, m->o.dz);
+    a.part = mat<float>(m, m->o.part);
+    a.cpart = mat<float>(m, m->o.cpart);
+    a.lpart = mat<double>(m, m->o.lpart);
+    a.grad = G;
+    a.grad2 = grad_out;
+    a.loss = loss_out;
+    a.batch = batch;
+    a.n_params = (long)m->P;
+    a.n_bias = (int)m->n_bias;
+    return mdev(m, launch_fused_backward(a, m->stream), "backward");
   } else {
     const uint16_t* act = mat<uint16_t>(m, m->o.act);
     const uint16_t* Wb = mat<uint16_t>(m, m->o.Wbf);
@@ -275,7 +341,7 @@ SUBADMM_API int subadmm_mlp_backward(subadmm_mlp* m, int32_t batch, const float*
       gw.sam = 1;
       gw.sak = N;
       gw.B = act + m->off_act[k];
-      gw.sbk = K;
+      gw.sbk = mlp_ld((int)K);
       gw.sbn = 1;
       gw.M = N;
       gw.N = K;
@@ -301,7 +367,7 @@ SUBADMM_API int subadmm_mlp_backward(subadmm_mlp* m, int32_t batch, const float*
         ga.sam = N;
         ga.sak = 1;
         ga.B = Wb + m->off_Wbf[k];
-        ga.sbk = K;
+        ga.sbk = mlp_ld((int)K);
         ga.sbn = 1;
         ga.M = batch;
         ga.N = K;
@@ -311,7 +377,7 @@ SUBADMM_API int subadmm_mlp_backward(subadmm_mlp* m, int32_t batch, const float*
         ga.b_n_fast = 1;
         ga.epi = EPI_RELU_MASK;
         ga.mask = act + m->off_act[k];
-        ga.ldm = K;
+        ga.ldm = mlp_ld((int)K);
         ga.C = dz[1 - cur];
         ga.ldc = K;
         rc = mdev(m, launch_gemm(ga, 1, m->stream), "input gradient gemm");
@@ -330,11 +396,15 @@ SUBADMM_API int subadmm_mlp_adam(subadmm_mlp* m, float lr, float beta1, float be
   if (rc) return rc;
   if (step < 1 || !(lr > 0.f) || !(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f) || !(eps > 0.f))
     return mfail(m, SUBADMM_E_ARG, "bad Adam hyper-parameters");
-  rc = mdev(m, launch_adam(mat<float>(m, m->o.P), mat<float>(m, m->o.G), mat<float>(m, m->o.M), mat<float>(m, m->o.V),
-                           (long)m->P, lr, beta1, beta2, eps, step, m->stream),
-            "adam");
-  if (rc) return rc;
-  return refresh_bf16(m);
+  AdamArgs a{};
+  a.g = mat<float>(m, m->o.G);
+  a.lr = lr;
+  a.b1 = beta1;
+  a.b2 = beta2;
+  a.eps = eps;
+  a.c1 = 1.f - powf(beta1, (float)step);
+  a.c2 = 1.f - powf(beta2, (float)step);
+  return update_params(m, a, "adam");
 }
 
 SUBADMM_API int subadmm_mlp_gather_rows(subadmm_mlp* m, const float* src, int64_t n_rows, int32_t width,
@@ -355,32 +425,15 @@ hipStream_t mlp_stream(const subadmm_mlp* m) { return m->stream; }
 uint64_t mlp_generation(const subadmm_mlp* m) { return m->gen; }
 
 int mlp_infer_on(subadmm_mlp* m, hipStream_t s, int32_t batch, const float* x, float* y) {
-  bool fits = m->L <= kInferMaxLayers;
-  for (int32_t k = 0; k <= m->L && fits; ++k) fits = m->w[k] <= kInferMaxWidth;
-  if (!fits) return mlp_forward_on(m, s, batch, x, y);
+  if (!m->fused) return mlp_forward_on(m, s, batch, x, y);
   int rc = check_bound(m);
   if (rc) return rc;
   if (batch < 0 || batch > m->max_batch) return mfail(m, SUBADMM_E_ARG, "batch out of range");
   if (!x || !y) return mfail(m, SUBADMM_E_ARG, "null input/output");
   m->last_batch = -1;  // no activations kept: a backward pass needs a forward first
-  MlpInferArgs a{};
-  a.x = x;
+  MlpFusedArgs a = fused_args(m, batch, x);
   a.y = y;
-  if (m->affine) {
-    a.scale = mat<float>(m, m->o.aff);
-    a.shift = a.scale + m->w[0];
-  }
-  a.Wbf = mat<uint16_t>(m, m->o.Wbf);
-  a.P = mat<float>(m, m->o.P);
-  a.batch = batch;
-  a.L = m->L;
-  for (int32_t k = 0; k <= m->L; ++k) a.w[k] = m->w[k];
-  for (int32_t k = 0; k < m->L; ++k) {
-    a.off_Wbf[k] = (long)m->off_Wbf[k];
-    a.off_b[k] = (long)m->off_b[k];
-    a.vec_w[k] = (m->w[k] % 8 == 0 && m->off_Wbf[k] % 8 == 0) ? 1 : 0;
-  }
-  return mdev(m, launch_mlp_infer(a, s), "inference");
+  return mdev(m, launch_fused_forward(a, s), "inference");
 }
 
 SUBADMM_API int subadmm_mlp_infer(subadmm_mlp* m, int32_t batch, const float* x, float* y) {

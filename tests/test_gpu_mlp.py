@@ -164,3 +164,45 @@ def test_fused_inference_equals_forward(widths, affine):
     if max(widths) <= 256:
         with pytest.raises(L.SubadmmError):
             net.backward(torch.zeros((1000, widths[-1]), device=net.device))
+
+
+@pytest.mark.parametrize("batch", [1, 31, 33, 129, 700])
+@pytest.mark.parametrize("widths", [[27, 256, 256, 256, 15], [5, 40, 33, 7], [3, 1], [250, 8, 129]])
+def test_whole_network_gradients_match_bf16_arithmetic(widths, batch):
+    """The whole-network backward pass at the edges of its row blocks, tiles and batch chunks
+    against FP64 products of the same BF16-rounded operands (weights, activations, layer
+    gradients).  Only FP32 accumulation differs: at most 256 terms, relative 1.5e-5, which moves a
+    share of ~1.5e-5 * 2^9 of the rounded entries by one BF16 step (2^-8), norm-wise ~3.5e-4;
+    bound 2e-3 per parameter block."""
+    rng = np.random.default_rng(sum(widths) * 1000 + batch)
+    p = _init(widths, rng).astype(np.float32)
+    x = rng.standard_normal((batch, widths[0])).astype(np.float32)
+    t = rng.standard_normal((batch, widths[-1])).astype(np.float32)
+    wt = rng.uniform(0.5, 1.5, t.shape).astype(np.float32)
+    net = _mlp(widths, batch)
+    net.set_params(p)
+    y = net.forward(x)
+    loss, g = net.backward(t, wt, want_grad=True)
+    g = g.cpu().numpy().astype(np.float64)
+    W, b, off = [], [], 0
+    for n0, n1 in zip(widths[:-1], widths[1:]):
+        W.append(bf16_round(p[off:off + n0 * n1]).reshape(n1, n0))
+        b.append(p[off + n0 * n1:off + n0 * n1 + n1].astype(np.float64))
+        off += n0 * n1 + n1
+    h = [bf16_round(x)]
+    for k in range(len(W) - 1):
+        h.append(bf16_round(np.maximum(h[-1] @ W[k].T + b[k], 0.0)))
+    out = h[-1] @ W[-1].T + b[-1]
+    np.testing.assert_allclose(y.cpu().numpy(), out, atol=2e-3 * np.linalg.norm(out) / np.sqrt(out.size) * 8)
+    d = wt * (out - t)
+    assert abs(float(loss.item()) - 0.5 * np.sum(wt * (out - t) ** 2)) <= 4e-3 * 0.5 * np.sum(wt * (out - t) ** 2)
+    ref = [None] * len(W)
+    for k in reversed(range(len(W))):
+        ref[k] = (bf16_round(d).T @ h[k], d.sum(0))
+        d = (bf16_round(d) @ W[k]) * (h[k] > 0)
+    off = 0
+    for k, (gw, gb) in enumerate(ref):
+        for r in (gw.ravel(), gb):
+            e = np.linalg.norm(g[off:off + r.size] - r)
+            assert e <= 2e-3 * np.linalg.norm(r) + 1e-12, (k, e, np.linalg.norm(r))
+            off += r.size
