@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "internal.hpp"
+#include "mfma.hpp"
 #include "rigid_device.hpp"
 
 namespace subadmm {
@@ -43,17 +44,21 @@ struct GroupWg {
   static constexpr bool kWave = false;
   __device__ static int rank() { return threadIdx.x; }
   __device__ static int size() { return blockDim.x; }
+  __device__ static int wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x) >> 6; }
+  __device__ static int waves() { return blockDim.x >> 6; }
   __device__ static void sync() { __syncthreads(); }
 };
 struct GroupWave {
   static constexpr bool kWave = true;
   __device__ static int rank() { return threadIdx.x & 63; }
   __device__ static int size() { return 64; }
+  __device__ static int wave() { return 0; }
+  __device__ static int waves() { return 1; }
   __device__ static void sync() { wave_lds_fence(); }
 };
 
-// Subsystems a single wave factorises: every column loop fits its 64 lanes (n <= 64, at
-// most 64 right-hand sides) and the working arrays fit the wave's share of LDS.
+// Subsystems a single wave factorises: small ones (n <= 64, at most 64 right-hand sides) whose
+// working arrays fit the wave's share of LDS.
 __host__ __device__ inline bool wave_factor_fits(int n, int nc, size_t cs, size_t slice) {
   return n <= 64 && nc + 1 <= 64 && factor_bytes(n, nc, cs) <= slice;
 }
@@ -68,37 +73,62 @@ __device__ inline double dev_sqrt<double>(double x) { return __builtin_sqrt(x); 
 // ------------------------------------------------------------------------------------
 // Per-step factorisation and slot-space operators (Alg. 1 factorisation step)
 // ------------------------------------------------------------------------------------
+// Entry i of p where `in`, else zero, without a branch around the load (p[0] is readable), so
+// that the loads of a tile product are in flight together.
+template <typename C, typename P>
+__device__ inline C tile_at(P p, int i, bool in) {
+  const C v = p[in ? i : 0];
+  return in ? v : (C)0;
+}
+
 // Factorisation of subsystem i by the thread group Grp (the workgroup or one wave), with its
 // working arrays at sm (LDS, or a global scratch area of the same layout); red (workgroup
-// form only) and bad are scratch shared by the group.  Every entry is formed by one thread
-// with the same arithmetic in either form; only the trace sums of Eq. 23 are added in
-// another grouping.
-template <typename T, typename C, typename Grp = GroupWg>
-__device__ __attribute__((always_inline)) inline void factor_body(const FactorArgs<T>& a, const int i, C* sm,
-                                                                 double (*red)[8], int& bad) {
+// form only) and bad are scratch shared by the group.
+//
+// Every O(n^2) and O(n^3) part is 16 x 16 tile products on the matrix cores: K's penalty term,
+// a left-looking blocked Cholesky whose diagonal tiles one wave factorises and inverts in
+// registers (the inverse replaces the tile), the block forward substitution of the right-hand
+// sides, H = T^T T, and the block back substitution.  A wave owns 16 right-hand sides from
+// start to end, so the substitutions have no barrier; the group synchronises three times per
+// 16 columns of the factor.  A tile's arithmetic does not depend on which wave forms it, so
+// the workgroup and the wave form agree except in the trace sums' grouping of Eq. 23.
+//
+// Bound by latency: the diagonal tiles (~2.7 us each, one wave) and chains of tile products; few
+// subsystems leave the matrix cores mostly idle.  Measured against the column-by-column form
+// (a barrier per column of the factor and per four pivot rows of the substitutions): 48 DOF with
+// 75 slot rows 78 -> 34 us, 127 DOF 260 -> 89 us, 285 DOF in device memory 4790 -> 483 us; the
+// legged batch's classes 80 -> 46 us and 85 -> 64 us (one subsystem per wave).
+template <typename T, typename C, typename Grp = GroupWg, typename P = C*, int kUnroll = 1>
+__device__ __attribute__((always_inline)) inline void factor_body(const FactorArgs<T>& a, const int i, P sm,
+                                                                 double (*red)[16], int& bad) {
   const int tid = Grp::rank();
   const int bd = Grp::size();
   const int n = a.t.sub_n[i];
   const int nc = a.t.sub_nc[i];
   // LDS leading dimensions are odd so that strided accesses fall in distinct banks
   const int ld = n | 1;
-  C* K = sm;                   // n x n, row-major with leading dimension ld, lower used
-  C* X = K + n * ld;           // (nc + 1) columns of length n, column stride ld: J rows, then b,
-                               // solved in place
-  C* Jl = X;                   // the first nc columns: J (nc x n, row-major, leading dimension ld)
-  C* sc = X + (nc + 1) * ld;   // Jacobi scaling 1/sqrt(K_rr)
-  C* dinv = sc + n;            // 1 / L_kk
+  P K = sm;                   // n x n, row-major with leading dimension ld, lower used
+  P X = K + n * ld;           // (nc + 1) columns of length n, column stride ld: J rows, then b,
+                              // solved in place
+  P Jl = X;                   // the first nc columns: J (nc x n, row-major, leading dimension ld)
+  P sc = X + (nc + 1) * ld;   // Jacobi scaling 1/sqrt(K_rr); n more entries are not used
 
   const T* A = a.A + a.t.sub_A[i];
   const T* J = a.J + a.t.sub_J[i];
   const T* b = a.b + a.t.sub_dof[i];
   if (tid == 0) bad = 0;
+  // t / n for t < 2^20 and quotients below 2^11 (n <= 512): (t + 1/2) / n lies 1 / 2n at least
+  // from a whole number, further than the rounding of the product with the reciprocal
+  const float inv_n = 1.0f / (float)n;
+  auto div_n = [&](int t) { return (int)(((float)t + 0.5f) * inv_n); };
+#pragma unroll 4
   for (int t = tid; t < n * n; t += bd) {
-    const int r = t / n, c = t - r * n;
+    const int r = div_n(t), c = t - r * n;
     K[r * ld + c] = (C)A[t];
   }
+#pragma unroll 4
   for (int t = tid; t < nc * n; t += bd) {
-    const int r = t / n, c = t - r * n;
+    const int r = div_n(t), c = t - r * n;
     Jl[r * ld + c] = (C)J[t];
   }
   for (int t = tid; t < n; t += bd) X[nc * ld + t] = (C)b[t];
@@ -108,8 +138,9 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   double trA = 0.0, trJ = 0.0;
   for (int t = tid; t < n; t += bd) trA += (double)K[t * ld + t];
   for (int t = tid; t < nc * n; t += bd) {
-    const C v = Jl[(t / n) * ld + t % n];
-    trJ += (double)v * (double)v;
+    const int r = div_n(t);
+    const C v = Jl[r * ld + t - r * n];
+    trJ = tfma((double)v, (double)v, trJ);
   }
   if constexpr (Grp::kWave) {
     trA = wave_sum(trA);
@@ -126,13 +157,32 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   if (a.rho > 0.0) beta = (C)a.rho;
   else beta = trJ > 0.0 ? (C)(trA / trJ) : (C)1;
 
-  // K += beta J^T J (lower triangle).
-  for (int t = tid; t < n * n; t += bd) {
-    const int r = t / n, c = t - r * n;
-    if (c <= r) {
-      C s = 0;
-      for (int k = 0; k < nc; ++k) s += Jl[k * ld + r] * Jl[k * ld + c];
-      K[r * ld + c] += beta * s;
+  typedef Mfma<C> M;
+  typedef typename M::V MV;
+  const int lane = threadIdx.x & 63, g = lane >> 4, cn = lane & 15;
+  const int wv = Grp::wave(), nwv = Grp::waves();
+  const int nt = (n + 15) >> 4;  // tile rows of K
+  // K += beta J^T J, a wave per lower tile (k runs over the rows of J)
+  for (int tt = wv; tt < nt * (nt + 1) / 2; tt += nwv) {
+    int I = 0;
+    while ((I + 1) * (I + 2) / 2 <= tt) ++I;
+    const int ra = 16 * I + cn, rb = 16 * (tt - I * (I + 1) / 2) + cn;
+    MV acc = {0, 0, 0, 0};
+#pragma unroll kUnroll
+    for (int k0 = 0; k0 < nc; k0 += 16) {
+      C av[4], bv[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + M::k(s, g);
+        av[s] = tile_at<C>(Jl, k * ld + ra, k < nc && ra < n);
+        bv[s] = tile_at<C>(Jl, k * ld + rb, k < nc && rb < n);
+      }
+      acc = M::mul(av, bv, acc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 16 * I + M::k(q, g);
+      if (r < n && rb <= r) K[r * ld + rb] = tfma(beta, (C)acc[q], (C)K[r * ld + rb]);
     }
   }
   Grp::sync();
@@ -144,168 +194,184 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   Grp::sync();
   // K_hat = S K S, J_hat = J S (S = diag(sc)).
   for (int t = tid; t < n * n; t += bd) {
-    const int r = t / n, c = t - r * n;
+    const int r = div_n(t), c = t - r * n;
     if (c <= r) K[r * ld + c] *= sc[r] * sc[c];
   }
   for (int t = tid; t < (nc + 1) * n; t += bd) {
-    const int r = t / n, c = t - r * n;
+    const int r = div_n(t), c = t - r * n;
     X[r * ld + c] *= sc[c];  // J_hat rows, then S b
   }
   Grp::sync();
 
-  // Right-looking Cholesky K_hat = L L^T in LDS, one barrier per column: step j updates the
-  // trailing lower triangle with the unscaled column j and pivot d_j (K -= k_j k_j^T / d_j),
-  // leaving column j as it is; a final pass scales column j by 1/sqrt(d_j).
-  for (int j = 0; j + 1 < n; ++j) {
-    const int m = n - j - 1;
-    const int R = bd / m;  // row groups (m < 64 <= bd)
-    const int cc = j + 1 + tid % m, rg = tid / m;
-    if (rg < R) {
-      const C dg = K[j * ld + j];
-      const C invd = dg > (C)0 ? (C)1 / dg : (C)1;
-      const C kc = K[cc * ld + j] * invd;
-      for (int rr = j + 1 + rg; rr < n; rr += R)
-        if (cc <= rr) K[rr * ld + cc] -= K[rr * ld + j] * kc;
+  // Cholesky factor L of K_hat, 16 columns at a time; diagonal tiles hold their inverses.
+  for (int p = 0; p < nt; ++p) {
+    const int p0 = 16 * p, jb = n - p0 < 16 ? n - p0 : 16;
+    if (p > 0) {
+      // U_Ip = K_Ip - sum_{k < p} L_Ik L_pk^T: the lane holds U[cn][row(q, g)]
+      for (int I = p + wv; I < nt; I += nwv) {
+        const int ri = 16 * I + cn;
+        MV acc = {0, 0, 0, 0};
+#pragma unroll kUnroll
+        for (int k0 = 0; k0 < p0; k0 += 16) {
+          C av[4], bv[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int k = k0 + M::k(s, g);
+            av[s] = tile_at<C>(K, (p0 + cn) * ld + k, cn < jb);
+            bv[s] = tile_at<C>(K, ri * ld + k, ri < n);
+          }
+          acc = M::mul(av, bv, acc);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = p0 + M::k(q, g);
+          if (ri < n && c < n && c <= ri) K[ri * ld + c] -= acc[q];
+        }
+      }
+      Grp::sync();
+    }
+    if (wv == 0) {
+      if (!diag_tile<C>(K + (p0 * ld + p0), ld, jb) && lane == 0) bad = 1;
     }
     Grp::sync();
+    if (p + 1 < nt) {
+      // L_Ip = U_Ip L_pp^-T (jb = 16: tiles below the diagonal follow a full one)
+      for (int I = p + 1 + wv; I < nt; I += nwv) {
+        const int ri = 16 * I + cn;
+        C av[4], bv[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int k = M::k(s, g);
+          av[s] = tile_at<C>(K, ri * ld + p0 + k, ri < n);
+          bv[s] = tile_at<C>(K, (p0 + cn) * ld + p0 + k, k <= cn);
+        }
+        MV out = {0, 0, 0, 0};
+        out = M::mul(av, bv, out);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = 16 * I + M::k(q, g);
+          if (r < n) K[r * ld + p0 + cn] = out[q];
+        }
+      }
+      Grp::sync();
+    }
   }
-  for (int j = tid; j < n; j += bd) {
-    C dg = K[j * ld + j];
-    if (!(dg > (C)0)) { bad = 1; dg = (C)1; }
-    dinv[j] = dev_sqrt<C>(dg);  // L_jj (dinv is reused for 1 / L_jj below)
-  }
-  Grp::sync();
-  for (int t = tid; t < n * n; t += bd) {
-    const int r = t / n, j = t - r * n;
-    if (j <= r) K[r * ld + j] = r == j ? dinv[j] : K[r * ld + j] / dinv[j];
-  }
-  Grp::sync();
 
-  // T = L^-1 [J_hat^T | S b] by forward substitution in place, then H = T_J^T T_J and
-  // d = T_J^T T_b (= J_hat K_hat^-1 J_hat^T and J_hat K_hat^-1 S b), then back substitution
-  // in place gives K_hat^-1 [J_hat^T | S b] for G and c.  With at most one right-hand side
-  // per thread: each sweep by columns of L for all right-hand sides at once, each step k
-  // parallel over (row, right-hand side) pairs with one barrier; X keeps the numerators,
-  // which are multiplied by 1/L_kk where used and once at the end of each sweep.
+  // T = L^-1 [J_hat^T | S b] by block forward substitution in place, then H = T_J^T T_J and
+  // d = T_J^T T_b (= J_hat K_hat^-1 J_hat^T and J_hat K_hat^-1 S b), then block back
+  // substitution in place gives K_hat^-1 [J_hat^T | S b] for G and c.  A lane reads back only
+  // the entries of X that it wrote itself.
   T* H = a.H + a.t.sub_H[i];
   T* dd = a.d + a.t.sub_slot[i];
-  const int m = nc + 1;
-  if (m <= bd) {
-    const int R = bd / m;  // row groups
-    const int c = tid % m, rg = tid / m;
-    const bool act = rg < R;
-    C* x = X + c * ld;
-    for (int r = tid; r < n; r += bd) dinv[r] = (C)1 / K[r * ld + r];
-    Grp::sync();
-    // Four pivot rows per barrier: every thread of column c forms the block's pivots in the
-    // unblocked order (so the result is the same), updates its trailing rows, and after the
-    // barrier (when no thread reads them any more) the row group 0 thread stores the block's
-    // completed numerators.
-    constexpr int B = 4;
-    for (int k = 0; k + 1 < n; k += B) {
-      C num[B], piv[B];
-      const int nb = n - k < B ? n - k : B;
-      if (act) {
+  T* G = a.G + a.t.sub_J[i];
+  T* cv = a.cvec + a.t.sub_dof[i];
+  const int m = nc + 1, nct = (m + 15) >> 4;
+  for (int ct = wv; ct < nct; ct += nwv) {
+    const int c = 16 * ct + cn;
+    P x = X + (c < m ? c : 0) * ld;
+    for (int I = 0; I < nt; ++I) {
+      const int i0 = 16 * I, ri = i0 + cn;
+      MV acc = {0, 0, 0, 0};
+#pragma unroll kUnroll
+      for (int k0 = 0; k0 < i0; k0 += 16) {
+        C av[4], bv[4];
 #pragma unroll
-        for (int q = 0; q < B; ++q) {
-          if (q < nb) {
-            C v = x[k + q];
-            for (int p = 0; p < q; ++p) v -= K[(k + q) * ld + k + p] * piv[p];
-            num[q] = v;
-            piv[q] = v * dinv[k + q];
-          }
+        for (int s = 0; s < 4; ++s) {
+          const int k = k0 + M::k(s, g);
+          av[s] = tile_at<C>(K, ri * ld + k, ri < n);
+          bv[s] = tile_at<C>(x, k, c < m);
         }
-        for (int r = k + B + rg; r < n; r += R) {
-          C v = x[r];
+        acc = M::mul(av, bv, acc);
+      }
+      C av[4], bv[4];
 #pragma unroll
-          for (int p = 0; p < B; ++p) v -= K[r * ld + k + p] * piv[p];
-          x[r] = v;
-        }
+      for (int s = 0; s < 4; ++s) {
+        const int k = M::k(s, g);
+        av[s] = tile_at<C>(K, ri * ld + i0 + k, k <= cn && ri < n);
+        const bool in = c < m && i0 + k < n;
+        bv[s] = in ? tile_at<C>(x, i0 + k, in) - acc[s] : (C)0;
       }
-      Grp::sync();
-      if (act && rg == 0) {
-        for (int q = 1; q < nb; ++q) x[k + q] = num[q];
-      }
-    }
-    Grp::sync();
-    if (act) {
-      for (int r = rg; r < n; r += R) x[r] *= dinv[r];
-    }
-    Grp::sync();
-    for (int t = tid; t < nc * (nc + 1); t += bd) {
-      const int cc = t / nc, r = t - cc * nc;
-      C s = 0;
-      for (int k = 0; k < n; ++k) s += X[r * ld + k] * X[cc * ld + k];
-      if (cc < nc) H[cc * nc + r] = (T)s;
-      else dd[r] = (T)s;
-    }
-    Grp::sync();
-    for (int k = n - 1; k > 0; k -= B) {
-      C num[B], piv[B];
-      const int nb = k + 1 < B ? k + 1 : B;
-      if (act) {
+      MV out = {0, 0, 0, 0};
+      out = M::mul(av, bv, out);
 #pragma unroll
-        for (int q = 0; q < B; ++q) {
-          if (q < nb) {
-            C v = x[k - q];
-            for (int p = 0; p < q; ++p) v -= K[(k - p) * ld + k - q] * piv[p];
-            num[q] = v;
-            piv[q] = v * dinv[k - q];
-          }
-        }
-        for (int r = rg; r + B <= k; r += R) {
-          C v = x[r];
-#pragma unroll
-          for (int p = 0; p < B; ++p) v -= K[(k - p) * ld + r] * piv[p];
-          x[r] = v;
-        }
-      }
-      Grp::sync();
-      if (act && rg == 0) {
-        for (int q = 1; q < nb; ++q) x[k - q] = num[q];
-      }
-    }
-    Grp::sync();
-    if (act) {
-      for (int r = rg; r < n; r += R) x[r] *= dinv[r];
-    }
-  } else {
-    for (int c = tid; c <= nc; c += bd) {  // one right-hand side per thread
-      C* x = X + c * ld;
-      for (int r = 0; r < n; ++r) {
-        C s = x[r];
-        for (int k = 0; k < r; ++k) s -= K[r * ld + k] * x[k];
-        x[r] = s / K[r * ld + r];
-      }
-    }
-    Grp::sync();
-    for (int t = tid; t < nc * (nc + 1); t += bd) {
-      const int cc = t / nc, r = t - cc * nc;
-      C s = 0;
-      for (int k = 0; k < n; ++k) s += X[r * ld + k] * X[cc * ld + k];
-      if (cc < nc) H[cc * nc + r] = (T)s;
-      else dd[r] = (T)s;
-    }
-    Grp::sync();
-    for (int c = tid; c <= nc; c += bd) {
-      C* x = X + c * ld;
-      for (int r = n - 1; r >= 0; --r) {
-        C s = x[r];
-        for (int k = r + 1; k < n; ++k) s -= K[k * ld + r] * x[k];
-        x[r] = s / K[r * ld + r];
+      for (int q = 0; q < 4; ++q) {
+        const int r = i0 + M::k(q, g);
+        if (c < m && r < n) x[r] = out[q];
       }
     }
   }
   Grp::sync();
-
-  // G = S X_J, c = S X_b.
-  T* G = a.G + a.t.sub_J[i];
-  T* cv = a.cvec + a.t.sub_dof[i];
-  for (int t = tid; t < (nc + 1) * n; t += bd) {
-    const int c = t / n, r = t - c * n;
-    const T v = (T)(sc[r] * X[c * ld + r]);
-    if (c < nc) G[c * n + r] = v;
-    else cv[r] = v;
+  for (int tt = wv; tt < nct * (nct + 1) / 2; tt += nwv) {
+    int I = 0;
+    while ((I + 1) * (I + 2) / 2 <= tt) ++I;
+    const int J = tt - I * (I + 1) / 2;
+    const int ca = 16 * I + cn, cb = 16 * J + cn;
+    P xa = X + (ca < m ? ca : 0) * ld;
+    P xb = X + (cb < m ? cb : 0) * ld;
+    MV acc = {0, 0, 0, 0};
+#pragma unroll kUnroll
+    for (int k0 = 0; k0 < n; k0 += 16) {
+      C av[4], bv[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + M::k(s, g);
+        av[s] = tile_at<C>(xa, k, ca < m && k < n);
+        bv[s] = tile_at<C>(xb, k, cb < m && k < n);
+      }
+      acc = M::mul(av, bv, acc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 16 * I + M::k(q, g);
+      const T v = (T)acc[q];
+      if (r < nc && cb < nc) {
+        H[cb * nc + r] = v;
+        H[r * nc + cb] = v;
+      } else if (r == nc && cb < nc) {
+        dd[cb] = v;
+      }
+    }
+  }
+  Grp::sync();
+  for (int ct = wv; ct < nct; ct += nwv) {
+    const int c = 16 * ct + cn;
+    P x = X + (c < m ? c : 0) * ld;
+    for (int I = nt - 1; I >= 0; --I) {
+      const int i0 = 16 * I;
+      MV acc = {0, 0, 0, 0};
+#pragma unroll kUnroll
+      for (int k0 = i0 + 16; k0 < n; k0 += 16) {
+        C av[4], bv[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int k = k0 + M::k(s, g);
+          av[s] = tile_at<C>(K, k * ld + i0 + cn, k < n);
+          bv[s] = tile_at<C>(x, k, c < m && k < n);
+        }
+        acc = M::mul(av, bv, acc);
+      }
+      C av[4], bv[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = M::k(s, g);
+        av[s] = tile_at<C>(K, (i0 + k) * ld + i0 + cn, cn <= k && i0 + k < n);
+        const bool in = c < m && i0 + k < n;
+        bv[s] = in ? tile_at<C>(x, i0 + k, in) - acc[s] : (C)0;
+      }
+      MV out = {0, 0, 0, 0};
+      out = M::mul(av, bv, out);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = i0 + M::k(q, g);
+        if (c < m && r < n) {
+          x[r] = out[q];
+          // G = S X_J, c = S X_b
+          const T v = (T)(sc[r] * out[q]);
+          if (c < nc) G[c * n + r] = v;
+          else cv[r] = v;
+        }
+      }
+    }
   }
   if (tid == 0) {
     a.beta[i] = (T)beta;
@@ -316,20 +382,21 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
 template <typename T, typename C>
 __global__ void __launch_bounds__(512) factor_kernel(FactorArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double red[2][8];
+  __shared__ double red[2][16];
   __shared__ int bad;
   factor_body<T, C>(a, a.order[a.first + blockIdx.x], reinterpret_cast<C*>(smem_raw), red, bad);
 }
 
+constexpr int kBigThreads = 1024;
 // Subsystems whose working arrays exceed the LDS: the same factorisation with its working
-// arrays in device memory (scr + off[i] bytes), one 512-thread workgroup each (a workgroup's
+// arrays in device memory (scr + off[i] bytes), one 1024-thread workgroup each (a workgroup's
 // barriers order its device-memory accesses as they do its LDS accesses).
 template <typename T, typename C>
-__global__ void __launch_bounds__(512) factor_global_kernel(FactorArgs<T> a, char* scr, const int64_t* off) {
-  __shared__ double red[2][8];
+__global__ void __launch_bounds__(kBigThreads) factor_global_kernel(FactorArgs<T> a, char* scr, const int64_t* off) {
+  __shared__ double red[2][16];
   __shared__ int bad;
   const int i = a.order[a.first + blockIdx.x];
-  factor_body<T, C>(a, i, reinterpret_cast<C*>(scr + off[i]), red, bad);
+  factor_body<T, C, GroupWg, C*, 4>(a, i, reinterpret_cast<C*>(scr + off[i]), red, bad);
 }
 
 // Small subsystems: each wave of a 256-thread workgroup factorises one subsystem in its
@@ -1396,9 +1463,9 @@ hipError_t launch_factor_global(const FactorArgs<T>& a, int count, int max_n, bo
   if (count == 0) return hipSuccess;
   if (max_n > kMaxFactorDof) return hipErrorInvalidValue;
   if (fp64)
-    hipLaunchKernelGGL((factor_global_kernel<T, double>), dim3(count), dim3(512), 0, s, a, scr, off);
+    hipLaunchKernelGGL((factor_global_kernel<T, double>), dim3(count), dim3(kBigThreads), 0, s, a, scr, off);
   else
-    hipLaunchKernelGGL((factor_global_kernel<T, T>), dim3(count), dim3(512), 0, s, a, scr, off);
+    hipLaunchKernelGGL((factor_global_kernel<T, T>), dim3(count), dim3(kBigThreads), 0, s, a, scr, off);
   return hipGetLastError();
 }
 
@@ -1455,13 +1522,32 @@ __device__ __attribute__((always_inline)) inline const StepsArgs<T>* phase_args(
   return reinterpret_cast<const StepsArgs<T>*>(v);
 }
 
+// The factorisations called out of line: inlined, their registers (the diagonal tiles' rows) cost
+// the iteration spills (512 legged scenes, two steps: 3.55 ms before the matrix-core form, 3.71
+// with it inlined).  The LDS area is passed as its LDS offset, so that it is addressed directly.
+template <typename T, typename C>
+__device__ __attribute__((noinline)) void factor_wave_outlined(const FactorArgs<T>& a, const int i, const uint32_t lds) {
+  __shared__ int bad[4];
+  factor_body<T, C, GroupWave>(a, i, (__attribute__((address_space(3))) C*)lds, nullptr, bad[threadIdx.x >> 6]);
+}
+template <typename T, typename C>
+__device__ __attribute__((noinline)) void factor_lds_outlined(const FactorArgs<T>& a, const int i, const uint32_t lds) {
+  __shared__ double red[2][16];
+  __shared__ int bad;
+  factor_body<T, C, GroupWg>(a, i, (__attribute__((address_space(3))) C*)lds, red, bad);
+}
+template <typename T, typename C>
+__device__ __attribute__((noinline)) void factor_global_outlined(const FactorArgs<T>& a, const int i, C* scr) {
+  __shared__ double red[2][16];
+  __shared__ int bad;
+  factor_body<T, C, GroupWg>(a, i, scr, red, bad);
+}
+
 template <typename T, typename C, int kLanes>
 __global__ void __launch_bounds__(256, 4) steps_kernel(const StepsArgs<T>* __restrict__ ap) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double fred[2][8];
-  __shared__ int fbad;
-  __shared__ int wbad[4];
   __shared__ __align__(16) T lred[2][8];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
   // workgroups are dispatched round-robin over the XCDs and their CUs in block order, so the
   // order decides which scenes share a CU
   const int sc = ap->sc_order[blockIdx.x];
@@ -1489,16 +1575,15 @@ __global__ void __launch_bounds__(256, 4) steps_kernel(const StepsArgs<T>* __res
       for (int i = sb; i < se; ++i) {
         if (!wave_factor_fits(a.l.t.sub_n[i], a.l.t.sub_nc[i], sizeof(C), slice)) continue;
         if (k++ % nwave == wv)
-          factor_body<T, C, GroupWave>(a.f, i, reinterpret_cast<C*>(smem_raw + (size_t)wv * slice), nullptr,
-                                       wbad[wv]);
+          factor_wave_outlined<T, C>(a.f, i, lds0 + (uint32_t)(wv * slice));
       }
       __syncthreads();
       for (int i = sb; i < se; ++i) {
         if (wave_factor_fits(a.l.t.sub_n[i], a.l.t.sub_nc[i], sizeof(C), slice)) continue;
         if (factor_bytes(a.l.t.sub_n[i], a.l.t.sub_nc[i], sizeof(C)) <= (size_t)a.lds_factor)
-          factor_body<T, C>(a.f, i, reinterpret_cast<C*>(smem_raw), fred, fbad);
+          factor_lds_outlined<T, C>(a.f, i, lds0);
         else
-          factor_body<T, C>(a.f, i, reinterpret_cast<C*>(a.fscr + a.sc_fscr[sc]), fred, fbad);
+          factor_global_outlined<T, C>(a.f, i, reinterpret_cast<C*>(a.fscr + a.sc_fscr[sc]));
         __syncthreads();
       }
     }

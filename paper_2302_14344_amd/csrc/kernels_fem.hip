@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "internal.hpp"
+#include "mfma.hpp"
 
 namespace subadmm {
 
@@ -209,42 +210,6 @@ __global__ void fem_rows_kernel(Topo t, FemModel f, const T* pos, double dt, T* 
 // ------------------------------------------------------------------------------------
 namespace {
 
-
-// 16 x 16 tile products on the matrix cores, FP64 (v_mfma_f64_16x16x4f64) and FP32
-// (v_mfma_f32_16x16x4f32).  A 16-deep product is four instructions s = 0..3; in each, lane l
-// supplies A[l % 16][k] and B[k][l % 16] for one k of the four, and the result lane l,
-// register r holds D[row][l % 16].  With g = l / 16:
-//   FP64: row = 4 r + g;   FP32: row = 4 g + r.
-// The products below take k = row(s, g) (Mfma<F>::k), so that a result serves as the B
-// operand of a following product as it stands; any other one-to-one choice of k only
-// reorders the sum of a tile product.
-typedef double v4f64 __attribute__((ext_vector_type(4)));
-typedef float v4f32 __attribute__((ext_vector_type(4)));
-
-template <typename F>
-struct Mfma;
-
-template <>
-struct Mfma<double> {
-  typedef v4f64 V;
-  static __device__ inline int k(int s, int g) { return 4 * s + g; }
-  static __device__ inline V mul(const double* a, const double* b, V c) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
-    return c;
-  }
-};
-
-template <>
-struct Mfma<float> {
-  typedef v4f32 V;
-  static __device__ inline int k(int s, int g) { return 4 * g + s; }
-  static __device__ inline V mul(const float* a, const float* b, V c) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], c, 0, 0, 0);
-    return c;
-  }
-};
 
 __device__ inline double fsqrt(double x) { return __builtin_sqrt(x); }
 __device__ inline float fsqrt(float x) { return __builtin_sqrtf(x); }
@@ -851,15 +816,6 @@ struct Quad<double> {
 // rest in LDS for the whole step; R = 0 reads them from device memory every iteration.
 constexpr int kResTiles = 35;
 constexpr int kMtClasses[] = {8, 12, 16, 19};
-
-template <int... Is, typename F>
-__device__ __forceinline__ void static_for_seq(std::integer_sequence<int, Is...>, F&& f) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_seq(std::make_integer_sequence<int, N>{}, f);
-}
 
 __host__ __device__ constexpr int tri_row(int t) {
   int I = 0;
