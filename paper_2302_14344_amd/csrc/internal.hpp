@@ -33,6 +33,7 @@ constexpr int kFactorThreads = 128;
 struct Topo {
   int32_t n_sub, n_if, n_scene;
   int32_t max_row_scene;    // interface rows (e, lambda) of the largest scene
+  int32_t max_multi_scene;  // interfaces of more than two members of the scene with the most
   const int32_t* sub_n;     // DOF per subsystem
   const int32_t* sub_nc;    // slot rows per subsystem
   const int32_t* sub_dof;   // DOF offset
@@ -129,6 +130,7 @@ struct LoopArgs {
   int32_t contact_model;  // 0: exact Signorini-Coulomb projection, 1: relaxed convex model
   const int32_t* skip_converged;  // if set: scenes with skip_converged[s] != 0 are left as they are
   long long* st_fallback;         // if set: incremented for every scene this launch iterates
+  int32_t multi_lds;              // set by the launcher: descriptors of multi-member interfaces in LDS
 };
 
 // Rigid model (maximal coordinates) in device memory.
@@ -253,6 +255,9 @@ struct ErrorArgs {
   double* out;               // per scene
   int32_t kinds;             // bit k: interfaces of kind k count
 };
+
+// Bytes of the iteration kernel's descriptor of an interface of more than two members.
+constexpr size_t kMultiDescF32 = 64, kMultiDescF64 = 96;
 
 // LDS budget of the multi-step kernel: four workgroups per CU (160 KB) while the scene's
 // iteration fits in it.

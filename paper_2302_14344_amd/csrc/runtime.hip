@@ -108,7 +108,7 @@ struct subadmm_problem {
   bool recording() const { return rec_xc || rec_xj || rec_tc || rec_tj || rec_wc || rec_wj; }
   int32_t team_block = 0;          // 0: team kernel not usable for this problem
   int64_t n_dof = 0, n_slot = 0, n_rows = 0, n_A = 0, n_J = 0, n_H = 0;
-  int32_t max_n = 0, max_nc = 0, max_slot_scene = 0, max_if_scene = 0, max_row_scene = 0, max_sub_scene = 0;
+  int32_t max_n = 0, max_nc = 0, max_slot_scene = 0, max_if_scene = 0, max_row_scene = 0, max_sub_scene = 0, max_multi_scene = 0;
   int64_t max_h_scene = 0;
   // factorisation launches: subsystems grouped by DOF count
   std::vector<int32_t> fac_order;
@@ -550,6 +550,7 @@ Topo make_topo(subadmm_problem* p) {
   t.n_if = p->n_if;
   t.n_scene = p->n_scene;
   t.max_row_scene = p->max_row_scene;
+  t.max_multi_scene = p->max_multi_scene;
   auto& o = p->o;
   t.sub_n = at<int32_t>(p, o.sub_n);
   t.sub_nc = at<int32_t>(p, o.sub_nc);
@@ -1128,6 +1129,9 @@ SUBADMM_API int subadmm_setup(const subadmm_subsystem* subs, int32_t n_sub, cons
     p->max_slot_scene = std::max(p->max_slot_scene, p->sc_slot[s + 1] - p->sc_slot[s]);
     p->max_row_scene = std::max(p->max_row_scene, p->if_row[p->sc_if[s + 1]] - p->if_row[p->sc_if[s]]);
     p->max_sub_scene = std::max(p->max_sub_scene, p->sc_sub[s + 1] - p->sc_sub[s]);
+    int32_t multi = 0;
+    for (int32_t j = p->sc_if[s]; j < p->sc_if[s + 1]; ++j) multi += p->if_nsub[j] > 2;
+    p->max_multi_scene = std::max(p->max_multi_scene, multi);
     p->max_if_scene = std::max(p->max_if_scene, p->sc_if[s + 1] - p->sc_if[s]);
     p->max_h_scene = std::max<int64_t>(p->max_h_scene, p->sub_H[p->sc_sub[s + 1]] - p->sub_H[p->sc_sub[s]]);
   }

@@ -90,3 +90,36 @@ def test_multi_member_measure():
     r = OP.constraint_error(p, p.J, p.e, out["v_hat"], out["lam"], _np(pr.beta()))
     assert r.max() > 0
     np.testing.assert_allclose(g, r, rtol=1e-10, atol=1e-13)
+
+
+@pytest.mark.parametrize("extra", [0, 4, 8])
+def test_four_member_couplings_at_the_edges_of_lds(extra):
+    """One scene of four 24-DOF subsystems joined by 33 four-member couplings (kinds in turn),
+    with ``extra`` one-member rows on the first.  The iteration's operators, vectors and offsets
+    take about 146 KB of LDS at 0, 150.8 KB at 4 and would take 155 KB at 8, of 153.6 KB: the
+    couplings' constants fit beside them, do not fit, and fit again once the operators stay in
+    device memory."""
+    print(f"extra {extra}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(151 + extra))
+    m, n = 33, 24
+    kind = np.array([(0, 2, 3)[j % 3] for j in range(m)] + [0] * extra, np.int32)
+    dim = np.array([2] * m + [1] * extra, np.int32)
+    mem = np.full((m + extra, 4), -1, np.int32)
+    mem[:m] = np.arange(4)
+    mem[m:, 0] = 0
+    nsub = np.array([4] * m + [1] * extra, np.int32)
+    nc = [2 * m + extra, 2 * m, 2 * m, 2 * m]
+    A = []
+    for _ in range(4):
+        q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        A.append(((q * rng.uniform(1.0, 10.0, n)) @ q.T).ravel())
+    p = S.AssembledProblem(sub_ndof=np.full(4, n, np.int32), sub_scene=np.zeros(4, np.int32), if_kind=kind, if_dim=dim,
+                           if_nsub=nsub, if_sub=mem, if_mu=np.zeros(m + extra), A=np.concatenate(A),
+                           b=rng.standard_normal(4 * n), J=rng.standard_normal(sum(nc) * n),
+                           e=rng.standard_normal(int(dim.sum())),
+                           if_k=np.where(kind == 3, rng.uniform(0.2, 2.0, m + extra), 0.0),
+                           if_alpha=np.where(kind == 3, rng.uniform(0.1, 1.0, m + extra), 0.0))
+    ref = O.solve(p, p.A, p.b, p.J, p.e, max_iters=80, tol=0.0, n_threads=4)
+    out, _, _ = _run(p, torch.float64, "default", 80, 0.0)
+    for k, r in (("v_hat", ref.v_hat), ("lam", ref.lam), ("z", ref.z), ("u", ref.u)):
+        np.testing.assert_allclose(out[k], r, atol=1e-9 * max(1.0, np.abs(r).max()), err_msg=k)
