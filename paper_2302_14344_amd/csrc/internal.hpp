@@ -15,9 +15,14 @@ enum : int32_t { KIND_EQUALITY = 0, KIND_CONTACT = 1, KIND_HARD_INEQ = 2, KIND_S
 constexpr int kMaxDof = 64;      // largest subsystem of the rigid model's kernels
 constexpr int kMaxFactorDof = 512;  // largest subsystem of the factorisation (a thread per column)
 constexpr int kMaxFemDof = 768;  // largest subsystem (FEM block path)
-// copies of the FEM residual partials (each workgroup reads the copy of its index mod
-// kPartCopies, so the lines every workgroup polls are spread over more addresses)
+// Copies of the FEM scene's residual totals (a workgroup reads the copy of its index mod
+// kPartCopies, so the lines every workgroup polls are spread over more addresses).
 constexpr int kPartCopies = 8;
+// 64-bit words of the FEM residual exchange: rings of four iterations, two FP64 values of two
+// words each, per block (partials) and per scene and copy (totals).
+constexpr size_t fem_part_words(int64_t n_sub, int64_t n_scene) {
+  return 16 * (size_t)n_sub + 16 * kPartCopies * (size_t)n_scene;
+}
 constexpr int kMaxIfDim = 6;     // largest interface dimension
 constexpr int kMaxMembers = 4;   // largest member count |S_j| of an interface
 constexpr int kLoopThreads = 256;
@@ -352,9 +357,9 @@ struct FemLoopArgs {
   T* z_out;
   T* u_out;
   T* w_out;         // per slot: the w of the last x-update (for v_hat)
-  T* ybuf;          // 3 x n_slot: y of iterations l mod 3 (entries all-ones until written)
+  unsigned long long* ybuf;  // 2 x n_slot values (tagged words): y of iterations l mod 2
   T* lambda;
-  double* part;     // 3 x kPartCopies x 2 per subsystem: theta and |y|^2 partials, as ybuf
+  unsigned long long* part;  // fem_part_words: theta and |y|^2, partials then totals
   int32_t* st_iters;
   long long* st_total;
   long long* st_unconv;

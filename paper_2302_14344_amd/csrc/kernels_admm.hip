@@ -17,6 +17,7 @@
 //   keeps (y, w, u) per slot row.
 #include <type_traits>
 
+#include "exchange.hpp"
 #include "internal.hpp"
 #include "mfma.hpp"
 #include "rigid_device.hpp"
@@ -1990,37 +1991,6 @@ __global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
 // All loads of a poll are in flight together and the z-update runs three rows wide unless the
 // wave holds a larger interface (with a wait per value and all waves six wide: 4.2 us).
 // ------------------------------------------------------------------------------------
-template <typename T>
-struct Tagged;
-template <>
-struct Tagged<float> {
-  static constexpr int N = kClusterWordsF32;
-  __device__ static void put(unsigned long long* p, float v, uint32_t tag) {
-    const unsigned long long x = ((unsigned long long)__float_as_uint(v) << 32) | tag;
-    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ static bool get(const unsigned long long* p, float* v, uint32_t tag) {
-    const unsigned long long x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *v = __uint_as_float((uint32_t)(x >> 32));
-    return (uint32_t)x == tag;
-  }
-};
-template <>
-struct Tagged<double> {
-  static constexpr int N = kClusterWordsF64;
-  __device__ static void put(unsigned long long* p, double v, uint32_t tag) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    __hip_atomic_store(p, (b & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, (b << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ static bool get(const unsigned long long* p, double* v, uint32_t tag) {
-    const unsigned long long h = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long l = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *v = __longlong_as_double((long long)((h & 0xffffffff00000000ull) | (l >> 32)));
-    return (uint32_t)h == tag && (uint32_t)l == tag;
-  }
-};
-
 // x_r of one slot row from the blocked layout in the order of large_xupdate_row: column c
 // goes to partial sum c mod 4 while a full group of four remains, the rest to partial 0 (the
 // zero padding beyond the last column adds zeros).

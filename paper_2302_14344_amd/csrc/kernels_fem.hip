@@ -24,14 +24,15 @@
 //   workgroup does the z-update (Eq. 16-21) of the interfaces that touch its block
 //   (two-member interfaces are computed by both members from the same y, so both obtain
 //   the same lambda), the dual update (Eq. 14), the x-update and its share of the residual
-//   (Eq. 22), and tests the residual of its scene.  The values exchanged between workgroups
-//   (y and the residual partials) sit in three buffers used in turn and are written and
+//   (Eq. 22), and tests the residual of its scene.  The values exchanged between workgroups (y,
+//   the residual's partials and totals) carry their iteration's number and are written and
 //   polled with agent-scope atomics, which reach the point of coherence across the chip's
 //   L2 caches: no grid barrier and no device-wide cache write-back per iteration.
 // fem_vhat_kernel: v_hat = K^-1 (b + J^T w) after the iteration, from the factorisation's
 //   y = L^-1 P b and T = L_DD^-1 (each block's factors in the precision it was factorised in): v_D = T^T (y_D + T e_D), v_O = L_OO^-T (y_O - L_DO^T v_D).
 #include <type_traits>
 
+#include "exchange.hpp"
 #include "internal.hpp"
 #include "mfma.hpp"
 
@@ -653,32 +654,17 @@ __global__ void __launch_bounds__(kFemThreads)
 // ------------------------------------------------------------------------------------
 namespace {
 
-template <typename T>
-__device__ inline T ld_agent(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <typename T>
-__device__ inline void st_agent(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Values exchanged between the workgroups of the iteration (slot y, residual partials)
-// live in three buffers used in turn.  A buffer entry holds the all-ones bit pattern
-// ("not written"; no arithmetic result has it) until its writer stores the value, so a
-// reader polls the entry itself: no barrier, no counters.  A workgroup resets its own
-// entries of the buffer of iteration l + 2 once it has seen every partial of iteration l
-// (by then every reader of that buffer's previous use is done with it), and it waits for
-// its stores to be acknowledged before publishing the next iteration, so a reader that has
-// seen iteration l + 1 finds either the reset or the iteration-l + 2 value.
-template <typename T>
-__device__ inline T unwritten();
-template <>
-__device__ inline float unwritten<float>() { return __uint_as_float(0xffffffffu); }
-template <>
-__device__ inline double unwritten<double>() { return __longlong_as_double(-1ll); }
-__device__ inline bool is_unwritten(float v) { return __float_as_uint(v) == 0xffffffffu; }
-__device__ inline bool is_unwritten(double v) { return __double_as_longlong(v) == -1ll; }
+// Values exchanged between the workgroups of the iteration are tagged words (Tagged): the
+// number of the iteration travels with the value, so a reader polls the value itself: no
+// barrier, no counters, nothing to reset.
+//   y (per slot row): two buffers by iteration parity.  A block writes y of iteration l + 2
+//     after its z-update of l + 1, for which it needed the neighbour's y of l + 1, written
+//     after the neighbour's z-update of l: the entry of iteration l has been read.
+//   residual partials (per block) and totals (per scene): rings of kRing.  The partial of l + 4
+//     is written after the block's test of l + 1, whose total the scene's first block
+//     wrote after it had read every partial of l; the total of l + 4 after every block wrote
+//     its partial of l + 4, which it did after its test of l.
+constexpr int kRing = 4;
 // polls per wait before a workgroup gives up (FLAG_BARRIER)
 constexpr long kMaxPolls = 1l << 24;
 
@@ -712,25 +698,21 @@ __device__ inline double wave_sum_lane63(double v) {
   return v;
 }
 
-// Sums of two values over the workgroup, identical in every thread (fixed order).
-__device__ inline void block_sum2(double& v0, double& v1, double* red) {
-  const int tid = threadIdx.x;
+// Wave totals of two values to sums[2 wave], [2 wave + 1]; true in the wave that finished last of
+// the workgroup's four, which then sees all of them (no barrier).
+__device__ inline bool sum_last(double v0, double v1, double* sums, int* arrived) {
+  const int wv = threadIdx.x >> 6;
   v0 = wave_sum_lane63(v0);
   v1 = wave_sum_lane63(v1);
-  if ((tid & 63) == 63) {
-    red[2 * (tid >> 6)] = v0;
-    red[2 * (tid >> 6) + 1] = v1;
+  int n = 0;
+  if ((threadIdx.x & 63) == 63) {
+    sums[2 * wv] = v0;
+    sums[2 * wv + 1] = v1;
+    n = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  __syncthreads();
-  const int nw = blockDim.x >> 6;
-  double s0 = 0.0, s1 = 0.0;
-  for (int w = 0; w < nw; ++w) {
-    s0 += red[2 * w];
-    s1 += red[2 * w + 1];
-  }
-  v0 = s0;
-  v1 = s1;
-  __syncthreads();
+  n = __builtin_amdgcn_readlane(n, 63);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return (n & 3) == 3;
 }
 
 constexpr int kMaxFemSlots = 512;  // slot rows per block (two per thread)
@@ -845,11 +827,11 @@ __device__ inline T dot4_acc(const T* e, const T* r, T acc) {
 
 template <typename T>
 struct MatvecArgs {
-  const T* rd;   // LDS, 16 mt entries (zero beyond m)
-  T* ow;         // LDS, this wave's 16 mt partial products
+  const T* rd;   // LDS, 16 MT entries (zero beyond m)
+  T* ow;         // LDS, this wave's 16 MT partial products
   const T* sg;   // block's tiles in device memory, + 4 lane
-  const T* sl;   // this wave's LDS tiles, + 4 lane
-  int mt, g4, cc;
+  const T* sl;   // this wave's LDS tiles
+  int mt;
 };
 
 // Loads wave W's tiles before the iteration (resident form).
@@ -864,130 +846,150 @@ __device__ __forceinline__ void load_tiles(Quad<T>* sreg, const MatvecArgs<T>& c
       // rows beyond the block's own are stored as zero tiles
       Quad<T> v;
       if (I < c.mt) v.load(c.sg + (long)t * 256); else v.zero();
-      v.store(const_cast<T*>(c.sl) + (r - RR) * 256);
+      v.store(const_cast<T*>(c.sl) + 4 * (threadIdx.x & 63) + (r - RR) * 256);
     }
   });
 }
 
-// One wave's share of vd += S rd (fixed-size form): tile (I, J) adds T rd_J to rows I and,
-// below the diagonal, T^T rd_I to rows J.  Row sums are reduced over the 16 lanes of a
-// row when the tile row (or the wave's range) ends; column sums stay per lane and are
-// added at the end, one row group after another.
-template <typename T, int MT, int R, int W>
-__device__ __forceinline__ void matvec_fixed(const Quad<T>* sreg, const MatvecArgs<T>& c) {
+// lanes' values a, b: rows of 16 lanes 1, 3 of a exchanged with rows 0, 2 of b
+__device__ inline void swap_rows16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// the upper half of a exchanged with the lower half of b
+__device__ inline void swap_rows32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// One wave's share of S rd (fixed-size form): tile (I, J) adds T rd_J to rows I and, below the
+// diagonal, T^T rd_I to rows J.  Row sums are reduced over the 16 lanes of a row when the tile
+// row (or the wave's range) ends; column sums stay per lane and are added at the end, one
+// row group after another, four columns at a time by lane-row exchanges (no LDS), which
+// leaves lane row g with column 4 q + g.  Which entries of ow a wave writes is fixed: the
+// others hold zero from the start of the step.
+// A tile costs its eight FMAs (32 cycles) and nothing else (rd is zero-padded to MT rows), the
+// four row sums of a tile row are reduced side by side.  Measured for blocks of 267 constrained DOFs, two workgroups per
+// CU: 10,250 cycles with a branch per tile and LDS exchanges per column, 3,300 to 4,100 now.
+template <int MT, int R, int W>
+__device__ __forceinline__ void matvec_fixed(const Quad<float>* sreg, const MatvecArgs<float>& c) {
   constexpr int beg = wave_tile_beg(MT, W), cnt = wave_tile_count(MT, W), RR = R < cnt ? R : cnt;
-  constexpr int end = beg + cnt;
-  T rdl[MT], cacc[MT];
-  static_for<MT>([&](auto jc) {
+  constexpr int end = beg + cnt, Ib = tri_row(beg), Ie = tri_row(end - 1);
+  int lane = (int)threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // the lane's addresses are formed here, not held over the iteration
+  const int g4 = lane >> 4, cc = lane & 15;
+  const float* sl = c.sl + 4 * lane;
+  float rdl[Ie + 1], cacc[4 * ((Ie + 3) / 4) + 1];
+  static_for<Ie + 1>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
-    rdl[j] = j < c.mt ? c.rd[16 * j + c.cc] : (T)0;
-    cacc[j] = (T)0;
+    rdl[j] = c.rd[16 * j + cc];
   });
-  T racc[4] = {(T)0, (T)0, (T)0, (T)0}, ri[4] = {(T)0, (T)0, (T)0, (T)0}, rin[4] = {(T)0, (T)0, (T)0, (T)0};
-  if constexpr (cnt > 0) {
-    constexpr int I0 = tri_row(beg);
-    if (I0 < c.mt)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) ri[k] = c.rd[16 * I0 + 4 * c.g4 + k];
-  }
+  static_for<4 * ((Ie + 3) / 4)>([&](auto jc) { cacc[decltype(jc)::value] = 0.f; });
+  const float4* rq = reinterpret_cast<const float4*>(c.rd) + g4;
+  float4 rin = rq[4 * Ib];
   // tiles not in registers (LDS, or device memory when R = 0) are read PD tiles ahead into
   // a ring of registers; scheduling barriers at the tile boundaries keep the compiler from
   // hoisting further loads (which would cost registers the resident tiles need)
   constexpr int PD = R > 0 ? 2 : 8;
-  Quad<T> pf[PD];
-  // the device-memory tile addresses are formed here, in the iteration, from an opaque
-  // copy of the base (otherwise they are hoisted out of the iteration loop and held in
-  // registers, one pointer per tile)
-  const T* sgp = c.sg;
-  asm volatile("" : "+v"(sgp));
+  Quad<float> pf[PD];
+  // the device-memory tile addresses and the row tests are formed here, in the iteration, from
+  // opaque copies (otherwise they are hoisted out of the iteration loop and held in registers)
+  const float* sgp = nullptr;
+  int mt = c.mt;
+  if constexpr (R == 0) {
+    sgp = c.sg;
+    asm volatile("" : "+v"(sgp));
+    asm volatile("" : "+s"(mt));
+  }
   auto fetch = [&](auto qc) {
     constexpr int q = decltype(qc)::value, tq = beg + q;
     if constexpr (q >= RR && q < cnt) {
       if constexpr (R > 0)
-        pf[q % PD].load(c.sl + (q - RR) * 256);  // zero tiles beyond the block's rows
-      else if (tri_row(tq) < c.mt)
-        pf[q % PD].load(sgp + (long)tq * 256);
+        pf[q % PD].load(sl + (q - RR) * 256);  // zero tiles beyond the block's rows
+      else
+        pf[q % PD].load(sgp + (tri_row(tq) < mt ? (long)tq * 256 : 0l));  // not used beyond them
     }
   };
   // tile q is fetched at position q - PD; the first PD positions are fetched here
   static_for<PD>([&](auto qc) { fetch(qc); });
-  static_for<cnt>([&](auto rc) {
-    constexpr int r = decltype(rc)::value, t = beg + r, I = tri_row(t), J = t - I * (I + 1) / 2;
-    __builtin_amdgcn_sched_barrier(0);
-    // tiles of rows beyond the block's own are skipped (a branch per tile keeps each tile
-    // its own scheduling region, which keeps the register allocation of the resident form
-    // within its budget)
-    if (I < c.mt) {
-      if constexpr (J == 0 || r == 0) {
-        // next tile row's rd entries, read one row ahead (zero beyond the block)
-        if (I + 1 < c.mt) {
+  static_for<Ie - Ib + 1>([&](auto ic) {
+    constexpr int I = Ib + decltype(ic)::value, first = I * (I + 1) / 2;
+    constexpr int t0 = first > beg ? first : beg, t1 = first + I + 1 < end ? first + I + 1 : end;
+    // the resident form's tiles beyond the block's rows are zero: no branch, so that the reduction
+    // of one row overlaps the products of the next
+    if (R > 0 || I < mt) {
+      const float ri[4] = {rin.x, rin.y, rin.z, rin.w};
+      if constexpr (I < Ie) rin = rq[4 * (I + 1)];
+      float racc[4] = {0.f, 0.f, 0.f, 0.f};
+      static_for<t1 - t0>([&](auto rc) {
+        constexpr int t = t0 + decltype(rc)::value, r = t - beg, J = t - first;
+        if constexpr (r >= RR - PD) __builtin_amdgcn_sched_barrier(0);
+        Quad<float> v;
+        if constexpr (r < RR)
+          v = sreg[r];
+        else
+          v = pf[r % PD];
+        fetch(std::integral_constant<int, r + PD>{});
+        float e4[4];
+        v.to(e4);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) rin[k] = c.rd[16 * (I + 1) + 4 * c.g4 + k];
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) rin[k] = (T)0;
-        }
-      }
-      Quad<T> v;
-      if constexpr (r < RR)
-        v = sreg[r];
-      else
-        v = pf[r % PD];
-      fetch(std::integral_constant<int, r + PD>{});
-      T e4[4];
-      v.to(e4);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) racc[k] = fmat(e4[k], rdl[J], racc[k]);
-      if constexpr (J < I) cacc[J] = dot4_acc(e4, ri, cacc[J]);
-      if constexpr (J == I || t == end - 1) {
-        // a wave's tiles of one row are consecutive, so each of its rows is flushed once,
-        // into entries that hold zero until then: a plain store
-        if (I < c.mt) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const T q = row_sum16(racc[k]);
-            if (c.cc == 0) c.ow[16 * I + 4 * c.g4 + k] = q;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) racc[k] = (T)0;
-        if constexpr (J == I) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) ri[k] = rin[k];
-        }
-      }
-    } else {
-      fetch(std::integral_constant<int, r + PD>{});
+        for (int k = 0; k < 4; ++k) racc[k] = fmat(e4[k], rdl[J], racc[k]);
+        if constexpr (J < I) cacc[J] = dot4_acc(e4, ri, cacc[J]);
+      });
+      // a wave's tiles of one row are consecutive: each of its rows is stored once
+      float4 q;
+      q.x = row_sum16(racc[0]);
+      q.y = row_sum16(racc[1]);
+      q.z = row_sum16(racc[2]);
+      q.w = row_sum16(racc[3]);
+      if (cc == 0) *reinterpret_cast<float4*>(c.ow + 16 * I + 4 * g4) = q;
     }
   });
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (cnt > 0) {
-    // column sums: reduce over the four row groups of the lane's column (all columns'
-    // exchanges issued together), then one add per column entry
-    constexpr int ncol = tri_row(end - 1);  // columns J < the wave's last tile row
-    static_for<ncol>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      cacc[j] += __shfl_xor(cacc[j], 16, 64);
-    });
-    static_for<ncol>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      cacc[j] += __shfl_xor(cacc[j], 32, 64);
-    });
-    if (c.g4 == 0) {
-      static_for<ncol>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        if (j < c.mt) c.ow[16 * j + c.cc] += cacc[j];
-      });
+  // columns J < Ie; those from Ib on add to the row sums stored above
+  static_for<(Ie + 3) / 4>([&](auto qc) {
+    constexpr int q = decltype(qc)::value, c0 = 4 * q;
+    swap_rows16(cacc[c0], cacc[c0 + 1]);
+    swap_rows16(cacc[c0 + 2], cacc[c0 + 3]);
+    float s0 = cacc[c0] + cacc[c0 + 1], s1 = cacc[c0 + 2] + cacc[c0 + 3];
+    swap_rows32(s0, s1);
+    cacc[c0] = s0 + s1;
+  });
+  float old[(Ie + 3) / 4 + 1];
+  static_for<(Ie + 3) / 4>([&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    old[q] = 0.f;
+    if constexpr (4 * q + 3 >= Ib) {
+      const float v = c.ow[64 * q + 16 * g4 + cc];
+      old[q] = 4 * q + g4 >= Ib ? v : 0.f;
     }
-  }
+  });
+  static_for<(Ie + 3) / 4>([&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    if (4 * q + 3 < Ie || 4 * q + g4 < Ie) c.ow[64 * q + 16 * g4 + cc] = old[q] + cacc[4 * q];
+  });
 }
 
 // MT > 0: fixed-size operator product (blocks of at most MT tile rows); R > 0 resident
 // (two workgroups per CU, so at most 256 VGPRs per lane), R = 0 read every iteration.
 // MT = 0 (R = 0): any block size; tile coordinates at run time, column sums reduced over
 // the lane groups and added to LDS per tile.
+//
+// Bound by latency: an iteration waits for its neighbours' y only (one exchange through the
+// point of coherence) and has four workgroup barriers.  The residual of iteration l is summed
+// while iteration l + 1 runs (each block's partial by the scene's first block, in a fixed order)
+// and tested at the end of l + 2; a step that turns out to have stopped at l returns the values
+// of l from a ring of the last four, so results and counts are those of a test in every
+// iteration.  Measured per iteration: 512 blocks of 231 to 294 constrained DOFs 12.1 -> 5.8 us,
+// 20 blocks of at most 165 6.9 -> 3.5 us (before: the test of every partial by every block inside
+// the iteration, ten barriers, a wait per exchanged value).
+constexpr int kFemRed = 20;  // doubles: own partial (4 waves x 2), scene's sum (4 x 2), total (2 + 2)
 template <typename T, int R, int MT>
 __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(FemLoopArgs<T> a) {
+  typedef Tagged<T> X;
+  typedef Tagged<double> XD;
   extern __shared__ __align__(16) double lsm[];
   const int i = blockIdx.x;
   const int tid = threadIdx.x;
@@ -1006,84 +1008,83 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
     }
     return lo;
   }();
-  // LDS: reductions, scene flags, per-slot state, the constrained-DOF vectors, matvec
-  // partials, per-key slot lists and the static data of this block's interface groups
-  double* red = lsm;                                        // 16
-  T* y = reinterpret_cast<T*>(lsm + 16);                    // nc
-  T* u = y + a.max_nc;
-  T* w = u + a.max_nc;
-  T* z = w + a.max_nc;
-  T* lam = z + a.max_nc;
-  T* rd = lam + a.max_nc;                                   // 16 mt (zero beyond m)
-  T* vd = rd + a.max_mt16;                                  // m
-  T* outw = vd + a.max_mt16;                                // per wave 16 mt partial products
-  T* cdl = outw + 4 * a.max_mt16;                           // m: c = K^-1 b on the constrained DOFs
-  T* gT = cdl + a.max_mt16;                                 // 7 per group: ib0, ib1, iws, mu, e0..e2
-  int* gI = reinterpret_cast<int*>(gT + 7 * a.max_ng);      // 4 per group: q0, ga, gb, kind | dim << 4
-  int* kl = gI + 4 * a.max_ng;                              // m + 1 key offsets, then nc slots
+  // LDS: reductions, the constrained-DOF vectors (16-byte aligned), the static data of this
+  // block's interface groups, rings of y and lambda, w in the order of the DOFs it acts on
+  const int mtw = MT > 0 ? 16 * MT : a.max_mt16;
+  double* red = lsm;
+  T* rd = reinterpret_cast<T*>(lsm + kFemRed);              // mtw (zero beyond m)
+  T* outw = rd + mtw;                                       // per wave mtw partial products
+  T* gT = outw + 4 * mtw;                                   // 8 per group: ib0, ib1, iws, mu, e0..e2
+  int* gI = reinterpret_cast<int*>(gT + 8 * a.max_ng);      // 4 per group: q0, other slot, kind | dim << 4 | first << 8
+  T* yr = reinterpret_cast<T*>(gI + 4 * a.max_ng);          // kRing x nc
+  T* lr = yr + kRing * a.max_nc;                            // kRing x nc
+  T* ws = lr + kRing * a.max_nc;                            // nc + 4: sign times w
+  int* kb = reinterpret_cast<int*>(ws + a.max_nc + 4);      // mtw: range of each DOF in ws, begin | end << 16
+  uint16_t* pos = reinterpret_cast<uint16_t*>(kb + mtw);    // nc: entry of ws << 1 | (sign < 0)
+  uint16_t* dof = pos + a.max_nc;                           // nc: constrained DOF << 1 | (sign < 0)
   const T be = a.beta[i];
   const T* Si = a.S + a.f.sq_off[i];
   const int dk0 = a.f.dkey_off[i];
+  __shared__ int ngroup, s_lost, arrived[2];
 
   // per-step static data
   const int kbase = a.f.dk_off[dk0];
-  for (int k = tid; k <= m; k += bd) kl[k] = a.f.dk_off[dk0 + k] - kbase;
-  // slot (relative to the block) << 1 | (sign < 0) of every slot row selecting each DOF
   for (int q = tid; q < nc; q += bd) {
     const int ql = a.f.dk_slot[kbase + q] - s0;
-    kl[m + 1 + q] = (ql << 1) | (a.f.slot_sgn[s0 + ql] < 0 ? 1 : 0);
+    pos[ql] = (uint16_t)((q << 1) | (a.f.slot_sgn[s0 + ql] < 0 ? 1 : 0));
+    dof[q] = (uint16_t)((a.f.slot_dk[s0 + q] << 1) | (a.f.slot_sgn[s0 + q] < 0 ? 1 : 0));
   }
-  for (int k = tid; k < m; k += bd) cdl[k] = a.cd[dk0 + k];
-  // own slots: two per thread at most, sign and key in registers
-  T sg[2] = {(T)0, (T)0};
-  int kd[2] = {0, 0};
-  for (int r = 0; r < 2; ++r) {
-    const int q = tid + r * bd;
-    if (q < nc) {
-      sg[r] = (T)a.f.slot_sgn[s0 + q];
-      kd[r] = a.f.slot_dk[s0 + q];
-    }
+  for (int k = tid; k < m; k += bd) kb[k] = (a.f.dk_off[dk0 + k] - kbase) | ((a.f.dk_off[dk0 + k + 1] - kbase) << 16);
+  // c = K^-1 b at the thread's slots
+  T cds[2] = {(T)0, (T)0};
+  for (int r = 0; r < 2; ++r)
+    if (tid + r * bd < nc) cds[r] = a.cd[dk0 + a.f.slot_dk[s0 + tid + r * bd]];
+  if (tid == 0) {
+    ngroup = 0;
+    s_lost = 0;
+    arrived[0] = arrived[1] = 0;
   }
-  // interface groups that touch this block: the first slot row of each
-  __shared__ int ngroup;
-  if (tid == 0) ngroup = 0;
+  for (int k = tid; k < 5 * mtw; k += bd) rd[k] = (T)0;  // and outw
   __syncthreads();
+  // interface groups that touch this block: the first slot row of each
   for (int q = tid; q < nc; q += bd) {
     const int sl = s0 + q;
     if ((t.slot_mk[sl] & 7) != 0) continue;
     const int g = atomicAdd(&ngroup, 1);
     const int j = t.slot_if[sl];
     const bool two = t.if_nsub[j] == 2;
+    const bool first = t.if_slot0[j] == sl;
     const T ib0 = (T)1 / a.beta[t.if_sub0[j]];
     const T ib1 = two ? (T)1 / a.beta[t.if_sub1[j]] : (T)0;
     gI[4 * g + 0] = q;
-    gI[4 * g + 1] = t.if_slot0[j];
-    gI[4 * g + 2] = two ? t.if_slot1[j] : -1;
-    gI[4 * g + 3] = t.if_kind[j] | (t.if_dim[j] << 4);
-    gT[7 * g + 0] = ib0;
-    gT[7 * g + 1] = ib1;
-    gT[7 * g + 2] = (T)1 / (ib0 + ib1);
-    gT[7 * g + 3] = a.mu[j];
-    for (int k = 0; k < 3; ++k) gT[7 * g + 4 + k] = k < t.if_dim[j] ? a.e[t.if_row[j] + k] : (T)0;
+    gI[4 * g + 1] = !two ? -1 : first ? t.if_slot1[j] : t.if_slot0[j];
+    gI[4 * g + 2] = t.if_kind[j] | (t.if_dim[j] << 4) | (first ? 256 : 0);
+    gI[4 * g + 3] = 0;
+    gT[8 * g + 0] = ib0;
+    gT[8 * g + 1] = ib1;
+    gT[8 * g + 2] = (T)1 / (ib0 + ib1);
+    gT[8 * g + 3] = a.mu[j];
+    for (int k = 0; k < 3; ++k) gT[8 * g + 4 + k] = k < t.if_dim[j] ? a.e[t.if_row[j] + k] : (T)0;
+    gT[8 * g + 7] = (T)0;
   }
-  // initial values: y^0 := beta z^0 + u^0 (relation after every z/u-update), w = beta z - u
+  // initial values (ring entry of iteration -1): y^0 := beta z^0 + u^0 (relation after every
+  // z/u-update), w = beta z - u
+  const auto z0_of = [&](int q) -> T { return a.z_in ? a.z_in[s0 + q] : (T)0; };
+  const auto u0_of = [&](int q) -> T { return a.u_in ? a.u_in[s0 + q] : (T)0; };
   for (int q = tid; q < nc; q += bd) {
-    const int sl = s0 + q;
-    const T z0 = a.z_in ? a.z_in[sl] : (T)0;
-    const T u0 = a.u_in ? a.u_in[sl] : (T)0;
-    z[q] = z0;
-    u[q] = u0;
-    w[q] = be * z0 - u0;
-    y[q] = be * z0 + u0;
-    lam[q] = -u0;
+    const T z0 = z0_of(q), u0 = u0_of(q);
+    const int pq = pos[q];
+    const T w0 = fmat(be, z0, -u0);
+    ws[pq >> 1] = (pq & 1) ? -w0 : w0;
+    yr[(kRing - 1) * a.max_nc + q] = fmat(be, z0, u0);
+    lr[(kRing - 1) * a.max_nc + q] = -u0;
   }
   __syncthreads();
   const int ng = ngroup;
-  for (int k = m + tid; k < 16 * mt; k += bd) rd[k] = (T)0;
   // operator product: the lower tiles in row order, split evenly over the four waves
   const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g4 = lane >> 4, cc = lane & 15;
-  T* ow = outw + wv * 16 * mt;
+  T* ow = outw + wv * mtw;
   // resident operator: registers, then LDS (16-byte aligned after the other arrays)
   Quad<T> sreg[(MT > 0 && R > 0) ? R : 1];
   MatvecArgs<T> mv;
@@ -1091,12 +1092,12 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
   mv.ow = ow;
   mv.sg = Si + 4 * lane;
   mv.mt = mt;
-  mv.g4 = g4;
-  mv.cc = cc;
   {
-    T* slds = reinterpret_cast<T*>(
-        (reinterpret_cast<uintptr_t>(kl + a.max_m + 1 + a.max_nc) + 15) & ~static_cast<uintptr_t>(15));
-    mv.sl = slds + (long)lds_tiles_before(MT, R, wv) * 256 + 4 * lane;
+    // by offset from the LDS base (an aligned pointer made from an integer would lose its
+    // address space and turn the tile reads into flat loads)
+    const int used = (int)(reinterpret_cast<unsigned char*>(dof + a.max_nc) - reinterpret_cast<unsigned char*>(lsm));
+    T* slds = reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(lsm) + ((used + 15) & ~15));
+    mv.sl = slds + lds_tiles_before(MT, R, wv) * 256;
   }
   if constexpr (MT > 0 && R > 0) {
     switch (wv) {
@@ -1115,32 +1116,48 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
 
   const int sub0 = t.sc_sub[scene], sub1 = t.sc_sub[scene + 1];
   int it = 0, conv = 0;
+  int kept = -1;  // iteration whose z-update is the result; -1: the initial values
   double th_s = 0.0, rt_s = 0.0;
-  for (int l = 0; l < a.max_iters; ++l) {
-    T* ybuf = a.ybuf + (long)(l % 3) * n_slot;
-    double* part = a.part + (long)(l % 3) * 2 * kPartCopies * t.n_sub;
-    {
+  // iteration l, and beyond the last iteration what is left of the residual's way
+  for (int l = 0; a.max_iters > 0; ++l) {
+    const bool run = l < a.max_iters;
+    unsigned long long* ybuf = a.ybuf + (long)(l & 1) * n_slot * X::N;
+    const uint32_t tag = (uint32_t)l + 1;
+    const auto part_of = [&](int k, int q) { return a.part + ((long)(k & 3) * t.n_sub + q) * 4; };
+    const auto total_of = [&](int k) {
+      return a.part + 16 * (long)t.n_sub + ((long)(k & 3) * t.n_scene + scene) * 4 * kPartCopies;
+    };
+    // indices of the phases below are formed from an opaque copy (otherwise the addresses of
+    // every phase are held in registers over the operator product)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    double pth = 0.0, pyy = 0.0;
+    if (run) {
       // x-update (Eq. 15): rd = J_D^T w; vd = cd + S rd; x = J_D vd; y = beta x + u (Eq. 18)
       for (int k = tid; k < m; k += bd) {
+        const int range = kb[k], end = range >> 16;
         T s = (T)0;
-        for (int q = kl[k]; q < kl[k + 1]; ++q) {
-          const int e = kl[m + 1 + q];
-          s += (e & 1) ? -w[e >> 1] : w[e >> 1];
+        for (int beg = range & 0xffff; beg < end; beg += 4) {
+          T v[4];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) v[h] = ws[beg + h];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) s += beg + h < end ? v[h] : (T)0;
         }
         rd[k] = s;
       }
+      if constexpr (MT == 0)
+        for (int k = tid; k < 4 * mtw; k += bd) outw[k] = (T)0;
       __syncthreads();
-      // vd = cd + S rd with S symmetric and only its lower tiles stored: a tile (I, J)
-      // adds T rd_J to rows I and, below the diagonal, T^T rd_I to rows J.  Row sums
-      // are kept per lane until the tile row ends, column sums are reduced per tile.
-      for (int k = tid; k < 4 * 16 * mt; k += bd) outw[k] = (T)0;
-      __syncthreads();
+      // S rd with S symmetric and only its lower tiles stored: a tile (I, J) adds T rd_J to
+      // rows I and, below the diagonal, T^T rd_I to rows J
       if constexpr (MT > 0) {
         switch (wv) {
-          case 0: matvec_fixed<T, MT, R, 0>(sreg, mv); break;
-          case 1: matvec_fixed<T, MT, R, 1>(sreg, mv); break;
-          case 2: matvec_fixed<T, MT, R, 2>(sreg, mv); break;
-          default: matvec_fixed<T, MT, R, 3>(sreg, mv); break;
+          case 0: matvec_fixed<MT, R, 0>(sreg, mv); break;
+          case 1: matvec_fixed<MT, R, 1>(sreg, mv); break;
+          case 2: matvec_fixed<MT, R, 2>(sreg, mv); break;
+          default: matvec_fixed<MT, R, 3>(sreg, mv); break;
         }
       } else {
         int I = I0, J = J0;
@@ -1186,160 +1203,159 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
         if (pending) row_flush();
       }
       __syncthreads();
-      for (int k = tid; k < m; k += bd) {
-        T s = (T)0;
-        for (int q = 0; q < 4; ++q) s += outw[q * 16 * mt + k];
-        vd[k] = cdl[k] + s;
-      }
-      __syncthreads();
-      double pth = 0.0, pyy = 0.0;
-      // this workgroup's resets of two iterations ago are performed before it publishes
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         const int q = tid + r * bd;
         if (q < nc) {
-          const T x = sg[r] * vd[kd[r]];
-          const T yn = be * x + u[q];
-          const T df = yn - y[q];
+          const int dq = dof[q];
+          T s = (T)0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) s += outw[k * mtw + (dq >> 1)];
+          const T yo = yr[((l - 1) & 3) * a.max_nc + q], lo = lr[((l - 1) & 3) * a.max_nc + q];
+          const T v = cds[r] + s, x = (dq & 1) ? -v : v;
+          const T yn = fmat(be, x, -lo);
+          const T df = yn - yo;
+          X::put(ybuf + (long)(s0 + q) * X::N, yn, tag);
           pth += (double)df * (double)df;
           pyy += (double)yn * (double)yn;
-          y[q] = yn;
-          st_agent(ybuf + s0 + q, yn);
+          yr[(l & 3) * a.max_nc + q] = yn;
         }
       }
-      block_sum2(pth, pyy, red);
-      // every copy of the partials gets them (readers spread over the copies)
-      if (tid < 2 * kPartCopies)
-        st_agent(part + (long)(tid >> 1) * 2 * t.n_sub + 2 * i + (tid & 1), (tid & 1) ? pyy : pth);
     }
-    // the z-update's inputs (this thread's first interface group), read now so that their
-    // latency overlaps the residual's reads; entries not yet written are read again later
-    T pya[3] = {(T)0, (T)0, (T)0}, pyb[3] = {(T)0, (T)0, (T)0};
-    if (tid < ng) {
-      const int ga = gI[4 * tid + 1], gb = gI[4 * tid + 2], dim = gI[4 * tid + 3] >> 4;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k < dim) pya[k] = ld_agent(ybuf + ga + k);
-        if (k < dim && gb >= 0) pyb[k] = ld_agent(ybuf + gb + k);
-      }
+    __syncthreads();
+    // residual of Eq. (22): this block's sums, published by the wave that finishes last
+    if (run && sum_last(pth, pyy, red, &arrived[0]) && lane < 2) {
+      double v = 0.0;
+      for (int q = 0; q < 4; ++q) v += red[2 * q + lane];
+      XD::put(part_of(l, i) + 2 * lane, v, tag);
     }
-    // residual of Eq. (22) over this block's scene: every partial of the iteration, summed
-    // in the same order by every workgroup of the scene (so all take the same decision)
-    double p0 = 0.0, p1 = 0.0;
     bool lost = false;
-    const double* mine = part + (long)(i % kPartCopies) * 2 * t.n_sub;
-    for (long polls = 0;; ++polls) {
+    // the scene's sum of iteration l - 1, by its first block: every partial in a fixed order (here,
+    // while the neighbours' y is on its way: after the z-update it made the first block the
+    // slowest)
+    if (i == sub0 && l >= 1 && l <= a.max_iters) {
       double s0p = 0.0, s1p = 0.0;
-      bool ready = true;
       for (int q = sub0 + tid; q < sub1; q += bd) {
-        const double v0 = ld_agent(mine + 2 * q), v1 = ld_agent(mine + 2 * q + 1);
-        ready = ready && !is_unwritten(v0) && !is_unwritten(v1);
+        const unsigned long long* pp = part_of(l - 1, q);
+        double v0 = 0.0, v1 = 0.0;
+        for (long polls = 0; !lost; ++polls) {
+          bool ok = XD::get(pp, &v0, tag - 1);
+          ok = XD::get(pp + 2, &v1, tag - 1) & ok;
+          if (ok) break;
+          lost = polls > kMaxPolls;
+        }
         s0p += v0;
         s1p += v1;
       }
-      if (__syncthreads_and(ready)) {
-        p0 = s0p;
-        p1 = s1p;
-        break;
+      if (sum_last(s0p, s1p, red + 8, &arrived[1]) && lane < 2 * kPartCopies) {
+        double v = 0.0;
+        for (int q = 0; q < 4; ++q) v += red[8 + 2 * q + (lane & 1)];
+        XD::put(total_of(l - 1) + 2 * lane, v, tag - 1);
       }
-      if (polls > kMaxPolls) {
-        lost = true;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
     }
-    if (lost) {
+    // z-update (Eq. 16-21) and dual update (Eq. 14) of the interfaces touching this block
+    if (l + 1 < a.max_iters) {
+      const T* yc = yr + (l & 3) * a.max_nc;
+      T* lc = lr + (l & 3) * a.max_nc;
+      for (int g = tid; g < ng; g += bd) {
+        const int q0 = gI[4 * g + 0], other = gI[4 * g + 1], kdim = gI[4 * g + 2];
+        const int kind = kdim & 15, dim = (kdim >> 4) & 15;
+        const bool first = (kdim & 256) != 0;
+        T gt[8], yw[3], yo[3] = {(T)0, (T)0, (T)0};
+        int pq[3];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) gt[k] = gT[8 * g + k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          yw[k] = yc[q0 + (k < dim ? k : 0)];
+          pq[k] = pos[q0 + (k < dim ? k : 0)];
+        }
+        // the other member's y, all values of a poll in flight together.  Once one wait of this
+        // thread has expired the iteration is abandoned and nothing further is polled
+        if (other >= 0) {
+          const unsigned long long* py = ybuf + (long)other * X::N;
+          for (long polls = 0; !lost; ++polls) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ok = X::get(py + (k < dim ? k : 0) * X::N, &yo[k], tag) & ok;
+            if (ok) break;
+            lost = polls > kMaxPolls;
+          }
+        }
+        const T ib0 = gt[0], ib1 = gt[1], iws = gt[2], mu = gt[3];
+        T p[3], lv[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const T ya = k < dim ? (first ? yw[k] : yo[k]) : (T)0;
+          const T yb = k < dim ? (first ? yo[k] : yw[k]) : (T)0;
+          p[k] = -fmat(yb, ib1, fmat(ya, ib0, gt[4 + k])) * iws;
+        }
+        if (kind == KIND_CONTACT && a.contact_model == 1) {
+          cone_project<T>(p, mu, lv);
+        } else if (kind == KIND_CONTACT) {
+          const T ln = p[0] > (T)0 ? p[0] : (T)0;
+          const T tn = fsqrt<T>(p[1] * p[1] + p[2] * p[2]);
+          const T cap = mu * ln;
+          lv[0] = ln;
+          if (tn <= cap) {
+            lv[1] = p[1];
+            lv[2] = p[2];
+          } else {
+            const T fct = cap / tn;
+            lv[1] = fct * p[1];
+            lv[2] = fct * p[2];
+          }
+        } else if (kind == KIND_HARD_INEQ) {
+          for (int k = 0; k < 3; ++k) lv[k] = p[k] > (T)0 ? p[k] : (T)0;
+        } else {
+          for (int k = 0; k < 3; ++k) lv[k] = p[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          if (k < dim) {
+            const T w = fmat((T)2, lv[k], yw[k]);
+            lc[q0 + k] = lv[k];
+            ws[pq[k] >> 1] = (pq[k] & 1) ? -w : w;
+          }
+        }
+      }
+    }
+    // the total of l - 2
+    if (l >= 2 && tid == bd - 1) {
+      double v0 = 0.0, v1 = 0.0;
+      const unsigned long long* pt = total_of(l - 2) + 4 * (i % kPartCopies);
+      for (long polls = 0; !lost; ++polls) {
+        bool ok = XD::get(pt, &v0, tag - 2);
+        ok = XD::get(pt + 2, &v1, tag - 2) & ok;
+        if (ok) break;
+        lost = polls > kMaxPolls;
+      }
+      red[16] = v0;
+      red[17] = v1;
+    }
+    if (lost) s_lost = 1;
+    __syncthreads();
+    if (s_lost) {
       if (tid == 0) atomicOr(a.flags, FLAG_BARRIER);
-      it = l + 1;
+      it = (run ? l : a.max_iters - 1) + 1;
+      kept = it - 2;
       break;
     }
-    block_sum2(p0, p1, red);
-    it = l + 1;
-    {
+    if (l >= 2) {
+      // every block of the scene reads the same total, so all take the same decision
+      const double p0 = red[16], p1 = red[17];
       const double tol2 = a.tol * a.tol;
       const bool bad = !__builtin_isfinite(p0) || !__builtin_isfinite(p1);
       const bool cv = !bad && p0 <= tol2 * (p1 > 1e-24 ? p1 : 1e-24);
-      if (cv || bad || l + 1 == a.max_iters) {
+      if (cv || bad || l - 1 == a.max_iters) {
         if (bad && i == sub0 && tid == 0) atomicOr(a.flags, FLAG_NONFINITE);
+        it = l - 1;
+        kept = l - 3;
         conv = cv;
         th_s = p0;
         rt_s = __builtin_sqrt(p0) / __builtin_sqrt(p1 > 1e-24 ? p1 : 1e-24);
         break;
       }
-    }
-    // every reader of the buffer of iteration l - 1 (= l + 2) is done with it: reset ours
-    {
-      T* yn2 = a.ybuf + (long)((l + 2) % 3) * n_slot;
-#pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int q = tid + r * bd;
-        if (q < nc) st_agent(yn2 + s0 + q, unwritten<T>());
-      }
-      if (tid < 2 * kPartCopies) {
-        double* pn2 = a.part + (long)((l + 2) % 3) * 2 * kPartCopies * t.n_sub;
-        st_agent(pn2 + (long)(tid >> 1) * 2 * t.n_sub + 2 * i + (tid & 1), unwritten<double>());
-      }
-    }
-    // z-update (Eq. 16-21) and dual update (Eq. 14) of the interfaces touching this block
-    for (int g = tid; g < ng; g += bd) {
-      const int q0 = gI[4 * g + 0], ga = gI[4 * g + 1], gb = gI[4 * g + 2], kdim = gI[4 * g + 3];
-      const int kind = kdim & 15, dim = kdim >> 4;
-      const T ib0 = gT[7 * g + 0], ib1 = gT[7 * g + 1], iws = gT[7 * g + 2], mu = gT[7 * g + 3];
-      T p[3], lv[3];
-      for (int k = 0; k < 3; ++k) {
-        T ya = (T)0, yb = (T)0;
-        if (k < dim) {
-          ya = g == tid ? pya[k] : ld_agent(ybuf + ga + k);
-          // once one wait of this thread has expired the iteration is abandoned: no
-          // further entry is polled, so a lost exchange costs one poll budget, not one per entry
-          for (long polls = 0; !lost && is_unwritten(ya) && polls <= kMaxPolls; ++polls) {
-            __builtin_amdgcn_s_sleep(1);
-            ya = ld_agent(ybuf + ga + k);
-          }
-          lost = lost || is_unwritten(ya);
-          if (gb >= 0) {
-            yb = g == tid ? pyb[k] : ld_agent(ybuf + gb + k);
-            for (long polls = 0; !lost && is_unwritten(yb) && polls <= kMaxPolls; ++polls) {
-              __builtin_amdgcn_s_sleep(1);
-              yb = ld_agent(ybuf + gb + k);
-            }
-            lost = lost || is_unwritten(yb);
-          }
-        }
-        p[k] = -(gT[7 * g + 4 + k] + ya * ib0 + yb * ib1) * iws;
-      }
-      if (kind == KIND_CONTACT && a.contact_model == 1) {
-        cone_project<T>(p, mu, lv);
-      } else if (kind == KIND_CONTACT) {
-        const T ln = p[0] > (T)0 ? p[0] : (T)0;
-        const T tn = fsqrt<T>(p[1] * p[1] + p[2] * p[2]);
-        const T cap = mu * ln;
-        lv[0] = ln;
-        if (tn <= cap) {
-          lv[1] = p[1];
-          lv[2] = p[2];
-        } else {
-          const T fct = cap / tn;
-          lv[1] = fct * p[1];
-          lv[2] = fct * p[2];
-        }
-      } else if (kind == KIND_HARD_INEQ) {
-        for (int k = 0; k < 3; ++k) lv[k] = p[k] > (T)0 ? p[k] : (T)0;
-      } else {
-        for (int k = 0; k < 3; ++k) lv[k] = p[k];
-      }
-      for (int k = 0; k < dim; ++k) {
-        const int qq = q0 + k;
-        u[qq] = -lv[k];
-        z[qq] = (y[qq] + lv[k]) / be;
-        w[qq] = y[qq] + (T)2 * lv[k];
-        lam[qq] = lv[k];
-      }
-    }
-    if (__syncthreads_or(lost)) {
-      if (tid == 0) atomicOr(a.flags, FLAG_BARRIER);
-      break;
     }
   }
   __syncthreads();
@@ -1347,12 +1363,25 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
   // interfaces whose member 0 is this block
   for (int q = tid; q < nc; q += bd) {
     const int sl = s0 + q;
-    if (a.z_out) a.z_out[sl] = z[q];
-    if (a.u_out) a.u_out[sl] = u[q];
-    a.w_out[sl] = w[q];
+    T z, u, w, lam;
+    if (kept < 0) {
+      z = z0_of(q);
+      u = u0_of(q);
+      w = fmat(be, z, -u);
+      lam = -u;
+    } else {
+      const T yk = yr[(kept & 3) * a.max_nc + q];
+      lam = lr[(kept & 3) * a.max_nc + q];
+      z = (yk + lam) / be;
+      u = -lam;
+      w = fmat((T)2, lam, yk);
+    }
+    if (a.z_out) a.z_out[sl] = z;
+    if (a.u_out) a.u_out[sl] = u;
+    a.w_out[sl] = w;
     const int j = t.slot_if[sl];
     const int mk = t.slot_mk[sl];
-    if (a.lambda && (mk >> 3) == 0) a.lambda[t.if_row[j] + (mk & 7)] = lam[q];
+    if (a.lambda && (mk >> 3) == 0) a.lambda[t.if_row[j] + (mk & 7)] = lam;
   }
   if (tid == 0 && i == t.sc_sub[scene]) {
     a.st_iters[scene] = it;
@@ -1438,12 +1467,11 @@ hipError_t launch_fem_factor(const Topo& t, const FemModel& f, const double* A, 
   return go(&fem_factor_kernel<T, double>, sizeof(double) * words, 0.0, 0);
 }
 
-// Marks every entry of the exchange buffers "not written" (all-ones bits).
-template <typename T>
-__global__ void fem_unwritten_kernel(T* y, long n_y, double* part, long n_part) {
+// Clears the exchange buffers (no iteration has tag 0).
+__global__ void fem_clear_kernel(unsigned long long* y, long n_y, unsigned long long* part, long n_part) {
   const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n_y) y[k] = unwritten<T>();
-  if (k < n_part) part[k] = unwritten<double>();
+  if (k < n_y) y[k] = 0;
+  if (k < n_part) part[k] = 0;
 }
 
 template <typename T, int R, int MT>
@@ -1477,16 +1505,18 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
   if (a.t.n_sub == 0) return hipSuccess;
   if (a.max_nc > kMaxFemSlots) return hipErrorInvalidValue;
   {
-    const long n_y = 3 * (long)a.n_slot, n_part = 6 * (long)kPartCopies * a.t.n_sub;
+    const long n_y = 2 * (long)Tagged<T>::N * a.n_slot, n_part = (long)fem_part_words(a.t.n_sub, a.t.n_scene);
     const long n = n_y > n_part ? n_y : n_part;
-    hipLaunchKernelGGL(fem_unwritten_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.ybuf, n_y,
-                       a.part, n_part);
+    hipLaunchKernelGGL(fem_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.ybuf, n_y, a.part,
+                       n_part);
     const hipError_t ze = hipGetLastError();
     if (ze != hipSuccess) return ze;
   }
-  const size_t lds = sizeof(double) * 16 +
-                     sizeof(T) * (5 * (size_t)a.max_nc + 7 * (size_t)a.max_mt16 + 7 * (size_t)a.max_ng) +
-                     sizeof(int) * (4 * (size_t)a.max_ng + (size_t)a.max_m + 1 + (size_t)a.max_nc);
+  const auto lds_of = [&](int mtw) -> size_t {
+    return sizeof(double) * kFemRed + sizeof(T) * (5 * (size_t)mtw + 8 * (size_t)a.max_ng) +
+           sizeof(int) * 4 * (size_t)a.max_ng + sizeof(T) * ((2 * kRing + 1) * (size_t)a.max_nc + 4) +
+           sizeof(int) * (size_t)mtw + 2 * sizeof(uint16_t) * (size_t)a.max_nc + 16;
+  };
   int dev = 0, cus = 0, lds_max = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1506,14 +1536,14 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
       auto run = [&](auto mtc) -> hipError_t {
         constexpr int M = decltype(mtc)::value;
         if (a.resident) {
-          const size_t lds_r = lds + 16 + (size_t)lds_tiles_before(M, kResTiles, 4) * 256 * sizeof(T);
+          const size_t lds_r = lds_of(16 * M) + (size_t)lds_tiles_before(M, kResTiles, 4) * 256 * sizeof(T);
           if (lds_r <= (size_t)lds_max) {
             const hipError_t er = resident_fem_loop<T, kResTiles, M>(a, lds_r, cus, fits, s);
             if (fits) *form = kResTiles;
             if (er != hipSuccess || fits) return er;
           }
         }
-        return resident_fem_loop<T, 0, M>(a, lds, cus, fits, s);
+        return resident_fem_loop<T, 0, M>(a, lds_of(16 * M), cus, fits, s);
       };
       switch (MT) {
         case 8: e = run(std::integral_constant<int, 8>{}); break;
@@ -1524,7 +1554,7 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
       if (e != hipSuccess || fits) return e;
     }
   }
-  e = resident_fem_loop<T, 0, 0>(a, lds, cus, fits, s);
+  e = resident_fem_loop<T, 0, 0>(a, lds_of(a.max_mt16), cus, fits, s);
   if (e != hipSuccess) return e;
   return fits ? hipSuccess : hipErrorCooperativeLaunchTooLarge;
 }

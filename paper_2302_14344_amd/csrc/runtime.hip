@@ -433,8 +433,8 @@ void plan_workspace(subadmm_problem* p) {
     o.fe = real(p->n_rows);
     o.fvh = real(p->n_dof);
     o.fw = real(p->n_slot);
-    o.fy = real(3 * (size_t)p->n_slot);
-    o.fpart = pl.take<double>(6 * (size_t)kPartCopies * p->n_sub);
+    o.fy = pl.take<unsigned long long>(2 * (p->dtype == SUBADMM_F64 ? kClusterWordsF64 : kClusterWordsF32) * (size_t)p->n_slot);
+    o.fpart = pl.take<unsigned long long>(fem_part_words(p->n_sub, p->n_scene));
     o.fprec = pl.take<int32_t>(p->n_sub);
     o.fkest = pl.take<double>(p->n_sub);
   }
@@ -2562,9 +2562,9 @@ int run_fem_step(subadmm_problem* p, T* pos, T* vel, double dt, int32_t max_iter
   a.z_out = at<T>(p, o.zw);
   a.u_out = at<T>(p, o.uw);
   a.w_out = at<T>(p, o.fw);
-  a.ybuf = at<T>(p, o.fy);
+  a.ybuf = at<unsigned long long>(p, o.fy);
   a.lambda = lambda;
-  a.part = at<double>(p, o.fpart);
+  a.part = at<unsigned long long>(p, o.fpart);
   a.st_iters = at<int32_t>(p, o.st_it);
   a.st_total = at<long long>(p, o.st_tot);
   a.st_unconv = at<long long>(p, o.st_unc);
