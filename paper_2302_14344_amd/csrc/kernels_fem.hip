@@ -30,6 +30,7 @@
 //   L2 caches: no grid barrier and no device-wide cache write-back per iteration.
 // fem_vhat_kernel: v_hat = K^-1 (b + J^T w) after the iteration, from the factorisation's
 //   y = L^-1 P b and T = L_DD^-1 (each block's factors in the precision it was factorised in): v_D = T^T (y_D + T e_D), v_O = L_OO^-T (y_O - L_DO^T v_D).
+#include <algorithm>
 #include <type_traits>
 
 #include "exchange.hpp"
@@ -215,6 +216,36 @@ namespace {
 __device__ inline double fsqrt(double x) { return __builtin_sqrt(x); }
 __device__ inline float fsqrt(float x) { return __builtin_sqrtf(x); }
 
+// Inverse of the ib x ib (ib <= 16) lower-triangular tile at L (leading dimension ldl) into X
+// (leading dimension ldx, strict upper triangle zero), one wave: lane r (mod 16) holds row r of
+// the tile and column r of the inverse; forward substitution of the identity, column by column.
+template <typename F>
+__device__ __attribute__((noinline)) void tri_inverse(const F* L, int ldl, int ib, F* X, int ldx) {
+  const int lane = threadIdx.x & 63, r = lane & 15;
+  F row[16], x[16];
+  static_for<16>([&](auto cc) {
+    constexpr int c = decltype(cc)::value;
+    const bool in = r < ib && c <= r;
+    const F v = L[in ? (long)r * ldl + c : 0];
+    row[c] = in ? v : (F)0;
+    x[c] = c == r ? (F)1 : (F)0;
+  });
+  static_for<16>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    if (j < ib) {
+      x[j] /= row_bcast<j>(row[j]);
+      static_for<15 - j>([&](auto qc) {
+        constexpr int c = j + 1 + decltype(qc)::value;
+        x[c] = tfma(-row_bcast<c>(row[j]), x[j], x[c]);
+      });
+    }
+  });
+  static_for<16>([&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    if (lane < ib && q < ib) X[(long)q * ldx + r] = q >= r ? x[q] : (F)0;
+  });
+}
+
 }  // namespace
 
 // Factor precision F.  F = float is a trial on every block: after its Cholesky factor it
@@ -225,13 +256,22 @@ __device__ inline float fsqrt(float x) { return __builtin_sqrtf(x); }
 // its L and T kept as FP32 in the same buffers.  F = double with gate = 1 runs only the
 // blocks the trial recorded; with gate = 0 it runs every block and records prec = 1 and its
 // own kappa_est.
+//
+// One block's factorisation is bound by the latency of its chain (load a tile row, multiply,
+// diagonal tile, next panel), two blocks a CU for 512 of them: eight waves, four tiles of loads
+// in flight per wave, the diagonal tile in registers (~6,400 cycles) beside the other tile rows of
+// its panel, and column blocks of T that a wave carries through without a barrier.  Measured,
+// FP64: 20 blocks of 225 DOFs 859 -> 231 us, 512 blocks of 375 DOFs 2868 -> 1685 us (before: four
+// waves, a load per product waited for, the diagonal tile in LDS column by column).
+constexpr int kFemFactorThreads = 512;
 template <typename T, typename F>
-__global__ void __launch_bounds__(kFemThreads)
+__global__ void __launch_bounds__(kFemFactorThreads, 4)
     fem_factor_kernel(Topo t, FemModel f, const double* A, double* b, double rho, T* beta, double* L, double* Tw,
                       T* S, T* cd, int32_t* flags, int32_t* prec, double* kest, double kmax, int gate) {
   typedef Mfma<F> M;
   typedef typename M::V V;
   constexpr bool kTrial = sizeof(F) == sizeof(float);
+  constexpr int kPad = 16 / (int)sizeof(F);  // panel rows 16 bytes apart in the banks
   __shared__ int s_bad;
   extern __shared__ __align__(16) double fsm_raw[];
   F* fsm = reinterpret_cast<F*>(fsm_raw);
@@ -247,174 +287,201 @@ __global__ void __launch_bounds__(kFemThreads)
   const double* Ai = A + t.sub_A[i];
   F* Li = reinterpret_cast<F*>(L + t.sub_A[i]);
   const int32_t* perm = f.perm + dof0;
-  const int pn = n > 32 ? n : 32;   // panel rows (at least 32)
-  F* red = fsm;                     // 256 -- the block-diagonal tile
-  F* dinv = fsm + kFemThreads;      // 16 x 16: inverse of the block-diagonal factor tile
-  F* panel = dinv + kNb * kNb;      // pn x kNb: one row panel of L
-  F* vec = panel + (long)pn * kNb;  // n
+  const int pn = n > 32 ? n : 32;   // panel columns (at least 32)
+  F* dinv = fsm;                    // 16 x 16: the diagonal tile, then its factor's inverse
+  F* panel = dinv + kNb * kNb;      // kNb x (pn + kPad): one row panel of L
+  F* vec = panel + (long)(pn + kPad) * kNb;  // n
   if (tid == 0) s_bad = 0;
 
   // Eq. (23): beta = Tr(A) / Tr(J^T J), Tr(J^T J) = slot rows (each selects one DOF); in
   // FP64 for either F (the first 256 doubles of LDS, before anything else uses them)
   double* redd = fsm_raw;
-  double tr = 0.0;
-  for (int r = tid; r < n; r += bd) tr += Ai[(long)r * n + r];
-  redd[tid] = tr;
+  if (tid < kFemThreads) {
+    double tr = 0.0;
+    for (int r = tid; r < n; r += kFemThreads) tr += Ai[(long)r * n + r];
+    redd[tid] = tr;
+  }
   __syncthreads();
-  for (int s = bd / 2; s > 0; s >>= 1) {
+  for (int s = kFemThreads / 2; s > 0; s >>= 1) {
     if (tid < s) redd[tid] += redd[tid + s];
     __syncthreads();
   }
   const double be = rho > 0.0 ? rho : (nc > 0 ? redd[0] / (double)nc : 1.0);
   __syncthreads();
   if (tid == 0) beta[i] = (T)be;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = bd >> 6;
 
-  // K = P (A + beta J^T J) P^T, lower triangle: a wave per row, lanes along it (the row
-  // of A is gathered through the permutation, kept in LDS)
+  // K = P (A + beta J^T J) P^T, lower triangle: a wave per four rows, lanes along them (the rows
+  // of A are gathered through the permutation, kept in LDS), eight loads in flight
   {
     int* pl = reinterpret_cast<int*>(vec);
     for (int r = tid; r < n; r += bd) pl[r] = perm[r];
     __syncthreads();
-    const int lane = tid & 63, nw = bd >> 6;
-    for (int r = tid >> 6; r < n; r += nw) {
-      const int pr = pl[r];
-      const double* Ar = Ai + (long)pr * n;
-      F* Lr = Li + (long)r * n;
-      for (int c = lane; c <= r; c += 64) {
-        double v = Ar[pl[c]];
-        if (c == r) v += be * (double)f.jtj[dof0 + pr];
-        Lr[c] = (F)v;
+    for (int r0 = 4 * wv; r0 < n; r0 += 4 * nwv)
+      for (int c0 = 0; c0 < r0 + 4 && c0 < n; c0 += 128) {
+        double v[4][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c = c0 + 64 * h + lane;
+          const int pc = pl[c < n ? c : 0];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int r = r0 + q;
+            v[q][h] = Ai[r < n && c <= r ? (long)pl[r] * n + pc : 0];
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int r = r0 + q, c = c0 + 64 * h + lane;
+            if (r < n && c <= r) {
+              double k = v[q][h];
+              if (c == r) k += be * (double)f.jtj[dof0 + pl[r]];
+              Li[(long)r * n + c] = (F)k;
+            }
+          }
       }
-    }
     __syncthreads();
   }
 
   // Left-looking blocked Cholesky on the matrix cores, 16-column panels J: every tile row
   // I >= J first forms U_IJ = K_IJ - sum_{K<J} L_IK L_JK^T (the row panel L_J,<J staged in
-  // LDS, shared by the waves), then the diagonal tile is factorised (one wave) and
-  // L_IJ = U_IJ L_JJ^-T for I > J.  b (permuted) is carried as one more row, below the
-  // matrix, so its factor row is y = L^-1 b (forward substitution for free).  K is read
-  // once and every L tile written once (the right-looking update read and wrote the whole
-  // trailing matrix per panel).
+  // LDS, shared by the waves), then the diagonal tile is factorised (the wave that formed it, while
+  // the others form theirs) and L_IJ = U_IJ L_JJ^-T for I > J.  b (permuted) is carried as one
+  // more row, below the matrix, so its factor row is y = L^-1 b (forward substitution for
+  // free).  K is read once and every L tile written once (the right-looking update read and
+  // wrote the whole trailing matrix per panel); a wave keeps its first kKeep tiles U_IJ in
+  // registers in between (4 cover blocks of up to 464 DOFs), further ones in their place.
+  constexpr int kKeep = 4;
   F* yrow = vec;  // LDS, n (the permutation list kept there is no longer needed)
   for (int c = tid; c < n; c += bd) yrow[c] = (F)b[dof0 + perm[c]];
   double* yout = b + dof0;
   const int nbn = (n + kNb - 1) / kNb;  // tile rows of K; tile row nbn holds b's row alone
-  const int lane = tid & 63, wv = tid >> 6, nwv = bd >> 6;
   const int g = lane >> 4, cn = lane & 15;
-  auto rowp = [&](int r) -> F* { return r < n ? Li + (long)r * n : yrow; };
-  auto rows_of = [&](int I) -> int { return I < nbn ? min(kNb, n - I * kNb) : 1; };
   __syncthreads();
   for (int J = 0; J < nbn; ++J) {
-    const int j0 = J * kNb, jb = min(kNb, n - j0);
-    // stage L_J,<J (jb x j0) in LDS, row stride j0
-    for (int q = tid; q < jb * j0; q += bd) {
-      const int rr = q / j0, c = q - rr * j0;
-      panel[q] = Li[(long)(j0 + rr) * n + c];
+    const int j0 = J * kNb, jb = min(kNb, n - j0), ps = j0 + kPad;
+    // stage L_J,<J (jb x j0) in LDS
+    for (int rr = wv; rr < jb; rr += nwv) {
+      const F* src = Li + (long)(j0 + rr) * n;
+#pragma unroll 4
+      for (int c = lane; c < j0; c += 64) panel[rr * ps + c] = src[c];
     }
     __syncthreads();
-    // U_IJ for the tile rows I >= J (the lane holds U_IJ[cn][row(r, g)], r = 0..3, and
-    // writes it over K_IJ; the same lane reads it back for L_IJ)
-    for (int I = J + wv; I <= nbn; I += nwv) {
-      const int i0 = I * kNb, ib = rows_of(I);
-      F* Ri = cn < ib ? rowp(i0 + cn) : nullptr;
-      V acc = {0, 0, 0, 0};
-      for (int K = 0; K < J; ++K) {
-        const int k0 = K * kNb;
-        F av[4], bv[4];
-#pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) {
-          const int kk = k0 + 4 * g + s2;
-          av[s2] = cn < jb ? panel[cn * j0 + kk] : (F)0;  // L_JK[cn][k]
-          bv[s2] = Ri ? Ri[kk] : (F)0;                   // L_IK[cn][k]
-        }
-        acc = M::mul(av, bv, acc);  // lane register r: (L_IK L_JK^T)[cn][row(r, g)]
-      }
+    // U_IJ of one tile row: the lane holds U_IJ[cn][k(r, g)], r = 0..3, of the row at Ri (a lane
+    // beyond the tile's rows or columns computes with valid entries that are not used)
+    auto u_tile = [&](auto Ri) -> V {
+      F kij[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int c = M::k(r, g);
-        if (Ri && c < jb) {
-          const F u = Ri[j0 + c] - acc[r];
-          if (I == J)
-            red[cn * kNb + c] = u;
-          else
-            Ri[j0 + c] = u;
-        }
+        kij[r] = Ri[j0 + (c < jb ? c : 0)];
       }
-    }
-    __syncthreads();
-    // diagonal tile: L_JJ (in place, lower) and L_JJ^-1 (dinv), one wave
-    if (wv == 0) {
-      F* dg = red;
-      for (int jj = 0; jj < jb; ++jj) {
-        if (lane == jj) {
-          F d = dg[jj * kNb + jj];
-          if (!(d > (F)0) || !__builtin_isfinite(d)) {
-            if (kTrial)
-              s_bad = 1;
-            else
-              atomicOr(flags, FLAG_NOT_SPD);
-            d = 1;
-          }
-          dg[jj * kNb + jj] = fsqrt(d);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane > jj && lane < jb) dg[lane * kNb + jj] /= dg[jj * kNb + jj];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane > jj && lane < jb)
-          for (int c = jj + 1; c <= lane; ++c) dg[lane * kNb + c] -= dg[lane * kNb + jj] * dg[c * kNb + jj];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
-      // inverse by forward substitution, a lane per column; zero outside the lower jb x jb
-      if (lane < kNb) {
-        const int c = lane;
-        F xcol[kNb];
+      V acc = {0, 0, 0, 0};
+      const F* pr = panel + cn * ps + 4 * g;
+      auto Rk = Ri + 4 * g;
+      auto step = [&](auto uc, int K) {
+        constexpr int U = decltype(uc)::value;
+        F av[U][4], bv[U][4];
 #pragma unroll
-        for (int r = 0; r < kNb; ++r) {
-          F v = 0;
-          if (r < jb && c < jb && r >= c) {
-            F sacc = r == c ? (F)1 : (F)0;
-            for (int p = c; p < r; ++p) sacc -= dg[r * kNb + p] * xcol[p];
-            v = sacc / dg[r * kNb + r];
-          }
-          xcol[r] = v;
-        }
+        for (int q = 0; q < U; ++q)
 #pragma unroll
-        for (int r = 0; r < kNb; ++r) dinv[r * kNb + c] = xcol[r];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      for (int q = lane; q < jb * jb; q += 64) {
-        const int rr = q / jb, c = q - rr * jb;
-        if (c <= rr) Li[(long)(j0 + rr) * n + j0 + c] = dg[rr * kNb + c];
-      }
-    }
-    __syncthreads();
-    // L_IJ = U_IJ L_JJ^-T for I > J (and b's row: y_J)
-    for (int I = J + wv; I <= nbn; I += nwv) {
-      if (I == J) continue;
-      const int i0 = I * kNb, ib = rows_of(I);
-      const F* Ri = cn < ib ? rowp(i0 + cn) : nullptr;
+          for (int s2 = 0; s2 < 4; ++s2) bv[q][s2] = Rk[(K + q) * kNb + s2];  // L_IK[cn][k]
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+          for (int s2 = 0; s2 < 4; ++s2) av[q][s2] = pr[(K + q) * kNb + s2];  // L_JK[cn][k]
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc = M::mul(av[q], bv[q], acc);  // (L_IK L_JK^T)[cn][k(r, g)]
+      };
+      int K = 0;
+      for (; K + 4 <= J; K += 4) step(std::integral_constant<int, 4>{}, K);
+      for (; K < J; ++K) step(std::integral_constant<int, 1>{}, K);
+      V u;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) u[r] = kij[r] - acc[r];
+      return u;
+    };
+    // L_IJ of one tile row from U_IJ, ib rows at Ri (leading dimension n)
+    auto l_tile = [&](const V& u, auto Ri, int ib) {
       F av[4], bv[4];
 #pragma unroll
       for (int s2 = 0; s2 < 4; ++s2) {
         const int c = M::k(s2, g);
-        av[s2] = (Ri && c < jb) ? Ri[j0 + c] : (F)0;  // U_IJ[cn][c]
-        bv[s2] = dinv[cn * kNb + c];                    // (L_JJ^-T)[c][cn]
+        av[s2] = c < jb ? u[s2] : (F)0;  // U_IJ[cn][c]
+        bv[s2] = dinv[cn * kNb + c];     // (L_JJ^-T)[c][cn]
       }
       V out = {0, 0, 0, 0};
-      out = M::mul(av, bv, out);  // lane register r: L_IJ[row(r, g)][cn]
+      out = M::mul(av, bv, out);  // lane register r: L_IJ[k(r, g)][cn]
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int rr = M::k(r, g);
-        if (rr < ib && cn < jb) rowp(i0 + rr)[j0 + cn] = out[r];
+        if (rr < ib && cn < jb) Ri[(long)rr * n + j0 + cn] = out[r];
+      }
+    };
+    V keep[kKeep];
+    if (wv == 0) {
+      const V u = u_tile(Li + (long)(j0 + (cn < jb ? cn : 0)) * n);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = M::k(r, g);
+        dinv[cn * kNb + c] = cn < jb && c <= cn ? u[r] : (F)0;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (!diag_tile<F, F*, F*>(dinv, kNb, jb, Li + (long)j0 * n + j0, n) && lane == 0) {
+        if (kTrial)
+          s_bad = 1;
+        else
+          atomicOr(flags, FLAG_NOT_SPD);
+      }
+    } else {
+      static_for<kKeep>([&](auto tc) {
+        constexpr int q = decltype(tc)::value;
+        const int I = J + wv + (nwv - 1) * q, i0 = I * kNb;
+        if (I < nbn)
+          keep[q] = u_tile(Li + (long)min(i0 + cn, n - 1) * n);
+        else if (I == nbn)
+          keep[q] = u_tile(yrow);
+      });
+      for (int I = J + wv + (nwv - 1) * kKeep; I <= nbn; I += nwv - 1) {
+        const int i0 = I * kNb;
+        auto out_of_place = [&](auto Ri, bool in) {
+          const V u = u_tile(Ri);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (in && M::k(r, g) < jb) Ri[j0 + M::k(r, g)] = u[r];
+        };
+        if (I < nbn)
+          out_of_place(Li + (long)min(i0 + cn, n - 1) * n, i0 + cn < n);
+        else
+          out_of_place(yrow, cn == 0);
+      }
+    }
+    __syncthreads();
+    if (wv > 0) {
+      static_for<kKeep>([&](auto tc) {
+        constexpr int q = decltype(tc)::value;
+        const int I = J + wv + (nwv - 1) * q, i0 = I * kNb;
+        if (I < nbn)
+          l_tile(keep[q], Li + (long)i0 * n, min(kNb, n - i0));
+        else if (I == nbn)
+          l_tile(keep[q], yrow, 1);
+      });
+      for (int I = J + wv + (nwv - 1) * kKeep; I <= nbn; I += nwv - 1) {
+        const int i0 = I * kNb;
+        auto in_place = [&](auto Ri, auto R0, int ib) {
+          V u;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) u[r] = Ri[j0 + (M::k(r, g) < jb ? M::k(r, g) : 0)];
+          l_tile(u, R0, ib);
+        };
+        if (I < nbn)
+          in_place(Li + (long)min(i0 + cn, n - 1) * n, Li + (long)i0 * n, min(kNb, n - i0));
+        else
+          in_place(yrow, yrow, 1);
       }
     }
     __syncthreads();
@@ -460,67 +527,66 @@ __global__ void __launch_bounds__(kFemThreads)
   }
 
   // T = L_DD^-1 (m x m lower, in this block's A storage: m^2 <= n^2), by 16-row blocks:
-  // T_II = L_II^-1 (forward substitution, a lane per column), then for I > J
-  // T_IJ = -T_II sum_{K=J}^{I-1} L_IK T_KJ, row block by row block, the column blocks J of
-  // a row block spread over the waves, every 16 x 16 product on the matrix cores.
+  // T_II = L_II^-1, then for I > J  T_IJ = -T_II sum_{K=J}^{I-1} L_IK T_KJ, column block by
+  // column block: one wave forms a column block from its diagonal down (no barrier), every
+  // 16 x 16 product on the matrix cores.  The long column blocks are dealt first.
   F* Ti = reinterpret_cast<F*>(Tw + t.sub_A[i]);
-  for (long k = tid; k < (long)m * m; k += bd) Ti[k] = 0;
-  __syncthreads();
   const int nbk = (m + kNb - 1) / kNb;
   const F* Ld = Li + (long)o * n + o;  // L_DD[r][c] = Ld[r * n + c]
   for (int I = wv; I < nbk; I += nwv) {
-    const int i0 = I * kNb, ib = min(kNb, m - i0);
-    if (lane < ib) {
-      const int c = lane;
-      F xcol[kNb];
-#pragma unroll
-      for (int r = 0; r < kNb; ++r) {
-        if (r < ib) {
-          F sacc = r == c ? (F)1 : (F)0;
-          for (int p = c; p < r; ++p) sacc -= Ld[(long)(i0 + r) * n + i0 + p] * xcol[p];
-          xcol[r] = r < c ? (F)0 : sacc / Ld[(long)(i0 + r) * n + i0 + r];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kNb; ++r)
-        if (r < ib && r >= c) Ti[(long)(i0 + r) * m + i0 + c] = xcol[r];
-    }
+    const int i0 = I * kNb;
+    tri_inverse<F>(Ld + (long)i0 * n + i0, n, min(kNb, m - i0), Ti + (long)i0 * m + i0, m);
   }
   __syncthreads();
-  for (int I = 1; I < nbk; ++I) {
-    const int i0 = I * kNb, ib = min(kNb, m - i0);
-    for (int J = wv; J < I; J += nwv) {
-      const int j0 = J * kNb;  // J < I: a full block
-      V acc = {0, 0, 0, 0};
-      for (int K = J; K < I; ++K) {
-        const int k0 = K * kNb;  // K < I: a full block
-        F av[4], bv[4];
-#pragma unroll
-        for (int s2 = 0; s2 < 4; ++s2) {
-          const int kk = M::k(s2, g);
-          av[s2] = cn < ib ? Ld[(long)(i0 + cn) * n + k0 + kk] : (F)0;
-          bv[s2] = Ti[(long)(k0 + kk) * m + j0 + cn];
-        }
-        acc = M::mul(av, bv, acc);
-      }
-      // T_IJ = -T_II acc: acc (lane: rows row(r, g) of column cn) is the B operand as it stands
-      F av[4], bv[4];
+  for (int q = 0; q * nwv < nbk; ++q) {
+    const int J = q * nwv + ((q & 1) ? nwv - 1 - wv : wv);
+    const int j0 = J * kNb;  // a full block where J < nbk - 1
+    for (int I = J + 1; I < nbk; ++I) {
+      const int i0 = I * kNb, ib = min(kNb, m - i0);
+      const F* Lr = Ld + (long)(i0 + (cn < ib ? cn : 0)) * n;
+      F tv[4];
 #pragma unroll
       for (int s2 = 0; s2 < 4; ++s2) {
         const int kk = M::k(s2, g);
-        av[s2] = (cn < ib && kk < ib) ? Ti[(long)(i0 + cn) * m + i0 + kk] : (F)0;
-        bv[s2] = acc[s2];
+        const F v = Ti[(long)(i0 + (cn < ib ? cn : 0)) * m + i0 + (kk < ib ? kk : 0)];
+        tv[s2] = kk < ib ? v : (F)0;
       }
+      V acc = {0, 0, 0, 0};
+      auto step = [&](auto uc, int K) {
+        constexpr int U = decltype(uc)::value;
+        F av[U][4], bv[U][4];
+#pragma unroll
+        for (int q2 = 0; q2 < U; ++q2)
+#pragma unroll
+          for (int s2 = 0; s2 < 4; ++s2) {
+            const int kk = (K + q2) * kNb + M::k(s2, g);  // K < I: a full block
+            av[q2][s2] = Lr[kk];
+            bv[q2][s2] = Ti[(long)kk * m + j0 + cn];
+          }
+#pragma unroll
+        for (int q2 = 0; q2 < U; ++q2) acc = M::mul(av[q2], bv[q2], acc);
+      };
+      int K = J;
+      for (; K + 4 <= I; K += 4) step(std::integral_constant<int, 4>{}, K);
+      for (; K < I; ++K) step(std::integral_constant<int, 1>{}, K);
+      // T_IJ = -T_II acc: acc (lane: rows k(r, g) of column cn) is the B operand as it stands
+      F bv[4];
+#pragma unroll
+      for (int s2 = 0; s2 < 4; ++s2) bv[s2] = acc[s2];
       V out = {0, 0, 0, 0};
-      out = M::mul(av, bv, out);
+      out = M::mul(tv, bv, out);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = M::k(r, g);
         if (row < ib) Ti[(long)(i0 + row) * m + j0 + cn] = -out[r];
       }
+      // the next row blocks read this one back in other lanes
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     }
-    __syncthreads();
   }
+  __syncthreads();
 
   // S = T^T T, lower 16 x 16 tiles: S_IJ = sum_{K >= I} T_KI^T T_KJ, a wave per tile.  Tile
   // layout of the iteration: entry (R, C) at ((R >> 2) * 16 + C) * 4 + (R & 3), so lane l
@@ -532,16 +598,34 @@ __global__ void __launch_bounds__(kFemThreads)
     while ((I + 1) * (I + 2) / 2 <= tt) ++I;
     const int J = tt - I * (I + 1) / 2;
     const int a0 = I * kNb, b0 = J * kNb;
+    const F* Ta = Ti + (a0 + cn < m ? a0 + cn : a0);
+    const F* Tb = Ti + (b0 + cn < m ? b0 + cn : b0);
     V acc = {0, 0, 0, 0};
-    for (int K = I; K < nbk; ++K) {
-      const int k0 = K * kNb, kb = min(kNb, m - k0);
+    auto step = [&](auto uc, int K) {  // full row blocks
+      constexpr int U = decltype(uc)::value;
+      F av[U][4], bv[U][4];
+#pragma unroll
+      for (int q2 = 0; q2 < U; ++q2)
+#pragma unroll
+        for (int s2 = 0; s2 < 4; ++s2) {
+          const int kk = (K + q2) * kNb + M::k(s2, g);
+          av[q2][s2] = Ta[(long)kk * m];
+          bv[q2][s2] = Tb[(long)kk * m];
+        }
+#pragma unroll
+      for (int q2 = 0; q2 < U; ++q2) acc = M::mul(av[q2], bv[q2], acc);
+    };
+    int K = I;
+    for (; K + 4 <= nbk - 1; K += 4) step(std::integral_constant<int, 4>{}, K);
+    for (; K < nbk - 1; ++K) step(std::integral_constant<int, 1>{}, K);
+    {  // the last row block
       F av[4], bv[4];
 #pragma unroll
       for (int s2 = 0; s2 < 4; ++s2) {
-        const int kk = M::k(s2, g);
-        const bool in = kk < kb;
-        av[s2] = (in && a0 + cn < m) ? Ti[(long)(k0 + kk) * m + a0 + cn] : (F)0;
-        bv[s2] = (in && b0 + cn < m) ? Ti[(long)(k0 + kk) * m + b0 + cn] : (F)0;
+        const int kk = K * kNb + M::k(s2, g);
+        const F va = Ta[(long)(kk < m ? kk : 0) * m], vb = Tb[(long)(kk < m ? kk : 0) * m];
+        av[s2] = kk < m ? va : (F)0;
+        bv[s2] = kk < m ? vb : (F)0;
       }
       acc = M::mul(av, bv, acc);
     }
@@ -552,7 +636,6 @@ __global__ void __launch_bounds__(kFemThreads)
           (a0 + row < m && b0 + cn < m) ? (T)acc[r] : (T)0;
     }
   }
-  __syncthreads();
 
   // y = L^-1 P b (permuted order) replaces b in its storage (b is not read again this step)
   for (int c = tid; c < n; c += bd) yout[c] = (double)yrow[c];
@@ -560,7 +643,15 @@ __global__ void __launch_bounds__(kFemThreads)
   // c_D = L_DD^-T y_D = T^T y_D
   for (int j = tid; j < m; j += bd) {
     double v = 0.0;
-    for (int k = j; k < m; ++k) v += (double)Ti[(long)k * m + j] * (double)yrow[o + k];
+    int k = j;
+    for (; k + 8 <= m; k += 8) {
+      F tk[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) tk[q] = Ti[(long)(k + q) * m + j];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += (double)tk[q] * (double)yrow[o + k + q];
+    }
+    for (; k < m; ++k) v += (double)Ti[(long)k * m + j] * (double)yrow[o + k];
     cd[f.dkey_off[i] + j] = (T)v;
   }
 }
@@ -1445,14 +1536,16 @@ hipError_t launch_fem_factor(const Topo& t, const FemModel& f, const double* A, 
   if (t.n_sub == 0) return hipSuccess;
   (void)max_m;
   const size_t pn = max_n > 32 ? (size_t)max_n : 32;
-  const size_t words = (size_t)kFemThreads + kNb * kNb + pn * kNb + (size_t)max_n;
+  // diagonal tile, row panel (rows padded by up to four entries), vector; at least the 256 doubles
+  // of the trace's reduction
+  const size_t words = std::max<size_t>(kNb * kNb + (pn + 4) * kNb + (size_t)max_n, 2 * kFemThreads);
   auto go = [&](auto kern, size_t lds, double km, int gate) -> hipError_t {
     if (lds > 64 * 1024) {
       const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (ea != hipSuccess) return ea;
     }
-    hipLaunchKernelGGL(kern, dim3(t.n_sub), dim3(kFemThreads), lds, s, t, f, A, b, rho, beta, L, tinv, S, cd, flags,
+    hipLaunchKernelGGL(kern, dim3(t.n_sub), dim3(kFemFactorThreads), lds, s, t, f, A, b, rho, beta, L, tinv, S, cd, flags,
                        prec, kest, km, gate);
     return hipGetLastError();
   };

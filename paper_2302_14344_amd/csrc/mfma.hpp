@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <type_traits>
 #include <utility>
 
@@ -95,8 +96,9 @@ __device__ inline float rsqrt_refined(float d) {
 // would otherwise weigh on every caller (inlined, the multi-step kernel's iteration spilled).
 // Bound by the chain of a column (broadcast, reciprocal square root, scale, broadcast, update:
 // ~300 cycles) and 120 updates: ~6,400 cycles for a full tile.
-template <typename C, typename P>
-__device__ __attribute__((noinline)) bool diag_tile(P D, int ld, int jb) {
+// keep (leading dimension ldk), where the caller gives one, receives L itself.
+template <typename C, typename P, typename Q = std::nullptr_t>
+__device__ __attribute__((noinline)) bool diag_tile(P D, int ld, int jb, Q keep = nullptr, int ldk = 0) {
   const int lane = threadIdx.x & 63, r = lane & 15;
   C row[16], x[16];
   static_for<16>([&](auto cc) {
@@ -116,6 +118,8 @@ __device__ __attribute__((noinline)) bool diag_tile(P D, int ld, int jb) {
       d = good ? d : (C)1;
       const C iv = rsqrt_refined(d);
       const C lj = row[j] * iv;  // L[r][j]
+      if constexpr (!std::is_same<Q, std::nullptr_t>::value)
+        if (lane < jb && r >= j) keep[(long)r * ldk + j] = r == j ? d * iv : lj;
       x[j] *= iv;
       static_for<15 - j>([&](auto qc) {
         constexpr int c = j + 1 + decltype(qc)::value;
