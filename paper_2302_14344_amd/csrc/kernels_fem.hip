@@ -789,21 +789,23 @@ __device__ inline double wave_sum_lane63(double v) {
   return v;
 }
 
-// Wave totals of two values to sums[2 wave], [2 wave + 1]; true in the wave that finished last of
-// the workgroup's four, which then sees all of them (no barrier).
-__device__ inline bool sum_last(double v0, double v1, double* sums, int* arrived) {
-  const int wv = threadIdx.x >> 6;
+// Wave totals of two values to sums[0], sums[1].
+__device__ inline void wave_sums(double v0, double v1, double* sums) {
   v0 = wave_sum_lane63(v0);
   v1 = wave_sum_lane63(v1);
-  int n = 0;
   if ((threadIdx.x & 63) == 63) {
-    sums[2 * wv] = v0;
-    sums[2 * wv + 1] = v1;
-    n = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    sums[0] = v0;
+    sums[1] = v1;
   }
+}
+// True in the wave that arrives last of a power of two of waves, which then sees what each wrote to
+// LDS before it arrived (no barrier).
+__device__ inline bool arrive_last(int* arrived, int waves) {
+  int n = 0;
+  if ((threadIdx.x & 63) == 63) n = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
   n = __builtin_amdgcn_readlane(n, 63);
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  return (n & 3) == 3;
+  return (n & (waves - 1)) == waves - 1;
 }
 
 constexpr int kMaxFemSlots = 512;  // slot rows per block (two per thread)
@@ -1073,8 +1075,8 @@ __device__ __forceinline__ void matvec_fixed(const Quad<float>* sreg, const Matv
 // while iteration l + 1 runs (each block's partial by the scene's first block, in a fixed order)
 // and tested at the end of l + 2; a step that turns out to have stopped at l returns the values
 // of l from a ring of the last four, so results and counts are those of a test in every
-// iteration.  Measured per iteration: 512 blocks of 231 to 294 constrained DOFs 12.1 -> 5.8 us,
-// 20 blocks of at most 165 6.9 -> 3.5 us (before: the test of every partial by every block inside
+// iteration.  Measured per iteration: 512 blocks of 231 to 294 constrained DOFs 12.1 -> 5.1 us,
+// 20 blocks of at most 165 6.9 -> 2.9 us (before: the test of every partial by every block inside
 // the iteration, ten barriers, a wait per exchanged value).
 constexpr int kFemRed = 20;  // doubles: own partial (4 waves x 2), scene's sum (4 x 2), total (2 + 2)
 template <typename T, int R, int MT>
@@ -1315,30 +1317,47 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
     }
     __syncthreads();
     // residual of Eq. (22): this block's sums, published by the wave that finishes last
-    if (run && sum_last(pth, pyy, red, &arrived[0]) && lane < 2) {
-      double v = 0.0;
-      for (int q = 0; q < 4; ++q) v += red[2 * q + lane];
-      XD::put(part_of(l, i) + 2 * lane, v, tag);
+    if (run) {
+      wave_sums(pth, pyy, red + 2 * wv);
+      if (arrive_last(&arrived[0], 4) && lane < 2) {
+        double v = 0.0;
+        for (int q = 0; q < 4; ++q) v += red[2 * q + lane];
+        XD::put(part_of(l, i) + 2 * lane, v, tag);
+      }
     }
     bool lost = false;
-    // the scene's sum of iteration l - 1, by its first block: every partial in a fixed order (here,
-    // while the neighbours' y is on its way: after the z-update it made the first block the
-    // slowest)
-    if (i == sub0 && l >= 1 && l <= a.max_iters) {
-      double s0p = 0.0, s1p = 0.0;
-      for (int q = sub0 + tid; q < sub1; q += bd) {
-        const unsigned long long* pp = part_of(l - 1, q);
-        double v0 = 0.0, v1 = 0.0;
+    // the scene's sum of iteration l - 1, by the waves of its first block that have the least of the
+    // z-update to do (the first block is the slowest otherwise): every partial, in the order of
+    // 256 strided sums, of which wave 3 forms 0..127 and wave 2 the others, two partials a lane
+    // in flight (four would spill the resident operator)
+    if (i == sub0 && wv >= 2 && l >= 1 && l <= a.max_iters) {
+      const int v0 = 2 * (3 - wv);
+      const unsigned long long* base = part_of(l - 1, 0);
+      double th[2] = {0.0, 0.0}, yy[2] = {0.0, 0.0};
+      for (int q0 = sub0 + 64 * v0 + lane; q0 < sub1; q0 += kFemThreads) {
+        double pt[2], py[2];
         for (long polls = 0; !lost; ++polls) {
-          bool ok = XD::get(pp, &v0, tag - 1);
-          ok = XD::get(pp + 2, &v1, tag - 1) & ok;
+          bool ok = true;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int q = q0 + 64 * h;
+            const unsigned long long* pp = base + 4u * (unsigned)(q < sub1 ? q : q0);
+            ok = XD::get(pp, &pt[h], tag - 1) & ok;
+            ok = XD::get(pp + 2, &py[h], tag - 1) & ok;
+          }
           if (ok) break;
           lost = polls > kMaxPolls;
         }
-        s0p += v0;
-        s1p += v1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool in = q0 + 64 * h < sub1;
+          th[h] += in ? pt[h] : 0.0;
+          yy[h] += in ? py[h] : 0.0;
+        }
       }
-      if (sum_last(s0p, s1p, red + 8, &arrived[1]) && lane < 2 * kPartCopies) {
+      wave_sums(th[0], yy[0], red + 8 + 2 * v0);
+      wave_sums(th[1], yy[1], red + 10 + 2 * v0);
+      if (arrive_last(&arrived[1], 2) && lane < 2 * kPartCopies) {
         double v = 0.0;
         for (int q = 0; q < 4; ++q) v += red[8 + 2 * q + (lane & 1)];
         XD::put(total_of(l - 1) + 2 * lane, v, tag - 1);
@@ -1412,7 +1431,7 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
       }
     }
     // the total of l - 2
-    if (l >= 2 && tid == bd - 1) {
+    if (l >= 2 && tid == 191) {  // wave 2
       double v0 = 0.0, v1 = 0.0;
       const unsigned long long* pt = total_of(l - 2) + 4 * (i % kPartCopies);
       for (long polls = 0; !lost; ++polls) {
