@@ -212,10 +212,6 @@ __global__ void fem_rows_kernel(Topo t, FemModel f, const T* pos, double dt, T* 
 // ------------------------------------------------------------------------------------
 namespace {
 
-
-__device__ inline double fsqrt(double x) { return __builtin_sqrt(x); }
-__device__ inline float fsqrt(float x) { return __builtin_sqrtf(x); }
-
 // Inverse of the ib x ib (ib <= 16) lower-triangular tile at L (leading dimension ldl) into X
 // (leading dimension ldx, strict upper triangle zero), one wave: lane r (mod 16) holds row r of
 // the tile and column r of the inverse; forward substitution of the identity, column by column.
@@ -662,7 +658,68 @@ __global__ void __launch_bounds__(kFemFactorThreads, 4)
 //   v_D = L_DD^-T (y_D + T e_D) = T^T (y_D + T e_D),   v_O = L_OO^-T (y_O - L_DO^T v_D).
 namespace {
 
+// One DPP step on a double (both 32-bit halves moved by the same control).
+template <int kCtrl, int kRowMask>
+__device__ inline double dpp_double(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), kCtrl, kRowMask, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, kRowMask, 0xF, false);
+  return __longlong_as_double(((long long)(unsigned)hi << 32) | (long long)(unsigned)lo);
+}
+
+// Sum over the 64 lanes of a wave in a fixed order (DPP only): pairs, quads, half rows and
+// rows of 16, then rows 0+1 into row 1 and rows 0..3 into row 3; lane 63 holds the total.
+__device__ inline double wave_sum_lane63(double v) {
+  v += dpp_double<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
+  v += dpp_double<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
+  v += dpp_double<0x141, 0xF>(v);  // row_half_mirror
+  v += dpp_double<0x140, 0xF>(v);  // row_mirror
+  v += dpp_double<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_double<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Value of one lane (uniform index) in all lanes.
+__device__ inline double wave_lane(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+constexpr int kVhatParts = 4;
+
+// kVhatParts partial sums of out[j] = sum_{k in [lo(j), m)} M[k ld + j] x[k], j < cols, by waves: a wave
+// per 64 columns and part of the rows, eight loads in flight; part p's sum goes to part[p cols + j].
+template <bool kLower, typename F>
+__device__ inline void vhat_columns(const F* M, long ld, int cols, int rows, const double* x, double* part) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nwv = blockDim.x >> 6;
+  const int chunks = (cols + 63) / 64, per = (rows + kVhatParts - 1) / kVhatParts;
+  for (int c = wv; c < chunks * kVhatParts; c += nwv) {
+    const int p = c / chunks, j = (c - p * chunks) * 64 + lane;
+    if (j >= cols) continue;
+    int k = p * per;
+    const int end = min(k + per, rows);
+    if (kLower && j > k) k = j;
+    double s = 0.0;
+    for (; k + 8 <= end; k += 8) {
+      F v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = M[(k + q) * ld + j];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s = __builtin_fma((double)v[q], x[k + q], s);
+    }
+    for (; k < end; ++k) s = __builtin_fma((double)M[k * ld + j], x[k], s);
+    part[p * cols + j] = s;
+  }
+}
+
 // The v_hat solve of one block with its factors L, T stored in precision F (sums in FP64).
+// Bound by the latency of its chain of products and of the back substitution: rows of T across
+// the lanes of a wave and its columns in four parts of the sum (both read whole lines, many loads
+// in flight), and the back substitution by 64 columns, in registers within them.  Measured, FP64
+// factors: 20 blocks of 225 DOFs 63 -> 26 us, 512 blocks of 375 DOFs 325 -> 105 us (before: a thread
+// per row or column, one load at a time, and a step of the back substitution per column).
 template <typename T, typename F>
 __device__ inline void fem_vhat_block(const Topo& t, const FemModel& f, int i, const F* Li, const F* Ti,
                                       const double* yb, const T* w, T* v_hat, double* vsm) {
@@ -672,11 +729,13 @@ __device__ inline void fem_vhat_block(const Topo& t, const FemModel& f, int i, c
   const int m = f.m[i];
   const int o = n - m;
   const int dof0 = t.sub_dof[i];
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = bd >> 6;
   const int32_t* perm = f.perm + dof0;
   const double* yi = yb + dof0;
-  double* v = vsm;       // n, permuted order
-  double* ed = v + n;    // m: e_D
-  double* zd = ed + m;   // m: y_D + T e_D
+  double* v = vsm;                    // n, permuted order
+  double* ed = v + n;                 // m: e_D
+  double* zd = ed + m;                // m: y_D + T e_D
+  double* part = zd + m;              // kVhatParts x max(m, o)
   for (int k = tid; k < m; k += bd) {
     const int g = f.dkey_off[i] + k;
     double s = 0.0;
@@ -687,40 +746,86 @@ __device__ inline void fem_vhat_block(const Topo& t, const FemModel& f, int i, c
     ed[k] = s;
   }
   __syncthreads();
-  for (int k = tid; k < m; k += bd) {
-    const F* Tk = Ti + (long)k * m;
-    double s = yi[o + k];
-    for (int p = 0; p <= k; ++p) s += (double)Tk[p] * ed[p];
-    zd[k] = s;
-  }
-  __syncthreads();
-  for (int j = tid; j < m; j += bd) {
-    double s = 0.0;
-    for (int k = j; k < m; ++k) s += (double)Ti[(long)k * m + j] * zd[k];
-    v[o + j] = s;
-  }
-  __syncthreads();
-  for (int c = tid; c < o; c += bd) {
-    double s = yi[c];
-    for (int r = 0; r < m; ++r) s -= (double)Li[(long)(o + r) * n + c] * v[o + r];
-    v[c] = s;
-  }
-  __syncthreads();
-  // L_OO^T v_O = (y_O - L_DO^T v_D): back substitution by columns, one wave
-  if (tid < 64) {
-    for (int c = o - 1; c >= 0; --c) {
-      if (tid == 0) v[c] /= (double)Li[(long)c * n + c];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const double vc = v[c];
-      for (int r = tid; r < c; r += 64) v[r] -= (double)Li[(long)c * n + r] * vc;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // z_D = y_D + T e_D: a wave per four rows
+  for (int k0 = 4 * wv; k0 < m; k0 += 4 * nwv) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int p = lane; p < k0 + 4; p += 64) {
+      F tv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool in = k0 + q < m && p <= k0 + q;
+        tv[q] = Ti[in ? (long)(k0 + q) * m + p : 0];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (k0 + q < m && p <= k0 + q) s[q] = __builtin_fma((double)tv[q], ed[p], s[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double r = wave_sum_lane63(s[q]);
+      if (lane == 63 && k0 + q < m) zd[k0 + q] = yi[o + k0 + q] + r;
     }
   }
   __syncthreads();
+  vhat_columns<true, F>(Ti, m, m, m, zd, part);
+  __syncthreads();
+  for (int j = tid; j < m; j += bd) {
+    double s = 0.0;
+    for (int p = 0; p < kVhatParts; ++p) s += part[p * m + j];
+    v[o + j] = s;
+  }
+  __syncthreads();
+  vhat_columns<false, F>(Li + (long)o * n, n, o, m, v + o, part);
+  __syncthreads();
+  for (int c = tid; c < o; c += bd) {
+    double s = 0.0;
+    for (int p = 0; p < kVhatParts; ++p) s += part[p * o + c];
+    v[c] = yi[c] - s;
+  }
+  __syncthreads();
+  // L_OO^T v_O = (y_O - L_DO^T v_D): back substitution, 64 columns at a time from the last.  Within
+  // them one wave, lane r holding column c0 + r; the rest of the columns by the workgroup.
+  for (int c0 = (o - 1) & ~63; c0 >= 0; c0 -= 64) {
+    const int cw = min(64, o - c0);
+    const F* Lc = Li + (long)c0 * n + c0;
+    if (wv == 0) {
+      double x = lane < cw ? v[c0 + lane] : 0.0;
+      const double dg = lane < cw ? (double)Lc[(long)lane * n + lane] : 1.0;
+      const double inv = 1.0 / dg;
+      for (int cb = (cw - 1) & ~7; cb >= 0; cb -= 8) {
+        F row[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) row[q] = Lc[cb + q < cw && lane < cb + q ? (long)(cb + q) * n + lane : 0];
+#pragma unroll
+        for (int q = 7; q >= 0; --q) {
+          if (cb + q < cw) {
+            // the quotient, corrected by its remainder
+            const double y0 = x * inv;
+            const double y1 = __builtin_fma(__builtin_fma(-dg, y0, x), inv, y0);
+            const double vc = wave_lane(y1, cb + q);
+            x = lane == cb + q ? y1 : lane < cb + q ? __builtin_fma(-(double)row[q], vc, x) : x;
+          }
+        }
+      }
+      if (lane < cw) v[c0 + lane] = x;
+    }
+    __syncthreads();
+    for (int r = tid; r < c0; r += bd) {
+      double s = v[r];
+      const F* Lr = Li + (long)c0 * n + r;
+      int c = cw - 1;
+      for (; c >= 7; c -= 8) {
+        F lv[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) lv[q] = Lr[(long)(c - q) * n];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s = __builtin_fma(-(double)lv[q], v[c0 + c - q], s);
+      }
+      for (; c >= 0; --c) s = __builtin_fma(-(double)Lr[(long)c * n], v[c0 + c], s);
+      v[r] = s;
+    }
+    __syncthreads();
+  }
   for (int r = tid; r < n; r += bd) v_hat[dof0 + perm[r]] = (T)v[r];
 }
 
@@ -728,7 +833,7 @@ __device__ inline void fem_vhat_block(const Topo& t, const FemModel& f, int i, c
 
 // prec[i] (written by the factorisation): 1 = the block's L and T are FP64, 0 = FP32.
 template <typename T>
-__global__ void __launch_bounds__(kFemThreads)
+__global__ void __launch_bounds__(kFemFactorThreads)
     fem_vhat_kernel(Topo t, FemModel f, const double* L, const double* Tw, const double* yb, const int32_t* prec,
                     const T* w, T* v_hat) {
   extern __shared__ __align__(16) double vsm[];
@@ -765,29 +870,6 @@ template <>
 __device__ inline float fsqrt<float>(float x) { return __builtin_sqrtf(x); }
 template <>
 __device__ inline double fsqrt<double>(double x) { return __builtin_sqrt(x); }
-
-// Fixed-order sum of two doubles per thread over the workgroup (deterministic): wave
-// butterflies, then the four wave totals in order.  Every thread gets the totals.
-// One DPP step on a double (both 32-bit halves moved by the same control).
-template <int kCtrl, int kRowMask>
-__device__ inline double dpp_double(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), kCtrl, kRowMask, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, kRowMask, 0xF, false);
-  return __longlong_as_double(((long long)(unsigned)hi << 32) | (long long)(unsigned)lo);
-}
-
-// Sum over the 64 lanes of a wave in a fixed order (DPP only): pairs, quads, half rows and
-// rows of 16, then rows 0+1 into row 1 and rows 0..3 into row 3; lane 63 holds the total.
-__device__ inline double wave_sum_lane63(double v) {
-  v += dpp_double<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
-  v += dpp_double<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
-  v += dpp_double<0x141, 0xF>(v);  // row_half_mirror
-  v += dpp_double<0x140, 0xF>(v);  // row_mirror
-  v += dpp_double<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-  v += dpp_double<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
 
 // Wave totals of two values to sums[0], sums[1].
 __device__ inline void wave_sums(double v0, double v1, double* sums) {
@@ -1675,8 +1757,8 @@ template <typename T>
 hipError_t launch_fem_vhat(const Topo& t, const FemModel& f, const double* L, const double* Tw, const double* y,
                            const int32_t* prec, const T* w, T* v_hat, int max_n, hipStream_t s) {
   if (t.n_sub == 0) return hipSuccess;
-  const size_t lds = sizeof(double) * 3 * (size_t)max_n;
-  hipLaunchKernelGGL(fem_vhat_kernel<T>, dim3(t.n_sub), dim3(kFemThreads), lds, s, t, f, L, Tw, y, prec, w, v_hat);
+  const size_t lds = sizeof(double) * (3 + kVhatParts) * (size_t)max_n;
+  hipLaunchKernelGGL(fem_vhat_kernel<T>, dim3(t.n_sub), dim3(kFemFactorThreads), lds, s, t, f, L, Tw, y, prec, w, v_hat);
   return hipGetLastError();
 }
 
