@@ -360,6 +360,7 @@ struct FemLoopArgs {
   unsigned long long* ybuf;  // 2 x n_slot values (tagged words): y of iterations l mod 2
   T* lambda;
   unsigned long long* part;  // fem_part_words: theta and |y|^2, partials then totals
+  T* ring;          // 8 per slot row: y and lambda of four iterations, where LDS does not hold them
   int32_t* st_iters;
   long long* st_total;
   long long* st_unconv;

@@ -1161,8 +1161,13 @@ __device__ __forceinline__ void matvec_fixed(const Quad<float>* sreg, const Matv
 // 20 blocks of at most 165 6.9 -> 2.9 us (before: the test of every partial by every block inside
 // the iteration, ten barriers, a wait per exchanged value).
 constexpr int kFemRed = 20;  // doubles: own partial (4 waves x 2), scene's sum (4 x 2), total (2 + 2)
-template <typename T, int R, int MT>
-__global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(FemLoopArgs<T> a) {
+//
+// Workgroups per CU, which bound the number of blocks of a launch: two of the resident form, three
+// or four of the others (the registers are held to that).  kFar: the ring in device memory, for
+// the launches whose blocks would not all be resident with it in LDS (large FP64 blocks in numbers).
+template <typename T, int R, int MT, bool kFar = false>
+__global__ void __launch_bounds__(kFemThreads, R > 0 ? 2 : MT == 0 ? (sizeof(T) == 8 ? 2 : 3) : MT <= 12 ? 4 : 3)
+    fem_loop_kernel(FemLoopArgs<T> a) {
   typedef Tagged<T> X;
   typedef Tagged<double> XD;
   extern __shared__ __align__(16) double lsm[];
@@ -1191,9 +1196,12 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
   T* outw = rd + mtw;                                       // per wave mtw partial products
   T* gT = outw + 4 * mtw;                                   // 8 per group: ib0, ib1, iws, mu, e0..e2
   int* gI = reinterpret_cast<int*>(gT + 8 * a.max_ng);      // 4 per group: q0, other slot, kind | dim << 4 | first << 8
-  T* yr = reinterpret_cast<T*>(gI + 4 * a.max_ng);          // kRing x nc
-  T* lr = yr + kRing * a.max_nc;                            // kRing x nc
-  T* ws = lr + kRing * a.max_nc;                            // nc + 4: sign times w
+  const int rs = kFar ? nc : a.max_nc;                      // ring stride
+  T* const near = reinterpret_cast<T*>(gI + 4 * a.max_ng);
+  T* yr;                                                    // kRing x nc
+  if constexpr (kFar) yr = a.ring + 2 * kRing * (long)s0; else yr = near;
+  T* lr = yr + kRing * rs;                                  // kRing x nc
+  T* ws = near + (kFar ? 0 : 2 * kRing * a.max_nc);         // nc + 4: sign times w
   int* kb = reinterpret_cast<int*>(ws + a.max_nc + 4);      // mtw: range of each DOF in ws, begin | end << 16
   uint16_t* pos = reinterpret_cast<uint16_t*>(kb + mtw);    // nc: entry of ws << 1 | (sign < 0)
   uint16_t* dof = pos + a.max_nc;                           // nc: constrained DOF << 1 | (sign < 0)
@@ -1251,8 +1259,8 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
     const int pq = pos[q];
     const T w0 = fmat(be, z0, -u0);
     ws[pq >> 1] = (pq & 1) ? -w0 : w0;
-    yr[(kRing - 1) * a.max_nc + q] = fmat(be, z0, u0);
-    lr[(kRing - 1) * a.max_nc + q] = -u0;
+    yr[(kRing - 1) * rs + q] = fmat(be, z0, u0);
+    lr[(kRing - 1) * rs + q] = -u0;
   }
   __syncthreads();
   const int ng = ngroup;
@@ -1386,14 +1394,14 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
           T s = (T)0;
 #pragma unroll
           for (int k = 0; k < 4; ++k) s += outw[k * mtw + (dq >> 1)];
-          const T yo = yr[((l - 1) & 3) * a.max_nc + q], lo = lr[((l - 1) & 3) * a.max_nc + q];
+          const T yo = yr[((l - 1) & 3) * rs + q], lo = lr[((l - 1) & 3) * rs + q];
           const T v = cds[r] + s, x = (dq & 1) ? -v : v;
           const T yn = fmat(be, x, -lo);
           const T df = yn - yo;
           X::put(ybuf + (long)(s0 + q) * X::N, yn, tag);
           pth += (double)df * (double)df;
           pyy += (double)yn * (double)yn;
-          yr[(l & 3) * a.max_nc + q] = yn;
+          yr[(l & 3) * rs + q] = yn;
         }
       }
     }
@@ -1447,8 +1455,8 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
     }
     // z-update (Eq. 16-21) and dual update (Eq. 14) of the interfaces touching this block
     if (l + 1 < a.max_iters) {
-      const T* yc = yr + (l & 3) * a.max_nc;
-      T* lc = lr + (l & 3) * a.max_nc;
+      const T* yc = yr + (l & 3) * rs;
+      T* lc = lr + (l & 3) * rs;
       for (int g = tid; g < ng; g += bd) {
         const int q0 = gI[4 * g + 0], other = gI[4 * g + 1], kdim = gI[4 * g + 2];
         const int kind = kdim & 15, dim = (kdim >> 4) & 15;
@@ -1562,8 +1570,8 @@ __global__ void __launch_bounds__(kFemThreads, MT > 0 ? 2 : 1) fem_loop_kernel(F
       w = fmat(be, z, -u);
       lam = -u;
     } else {
-      const T yk = yr[(kept & 3) * a.max_nc + q];
-      lam = lr[(kept & 3) * a.max_nc + q];
+      const T yk = yr[(kept & 3) * rs + q];
+      lam = lr[(kept & 3) * rs + q];
       z = (yk + lam) / be;
       u = -lam;
       w = fmat((T)2, lam, yk);
@@ -1668,10 +1676,10 @@ __global__ void fem_clear_kernel(unsigned long long* y, long n_y, unsigned long 
   if (k < n_part) part[k] = 0;
 }
 
-template <typename T, int R, int MT>
+template <typename T, int R, int MT, bool kFar = false>
 static hipError_t resident_fem_loop(const FemLoopArgs<T>& a, size_t lds, int cus, bool& fits, hipStream_t s) {
   int per_cu = 0;
-  const void* fn = reinterpret_cast<const void*>(&fem_loop_kernel<T, R, MT>);
+  const void* fn = reinterpret_cast<const void*>(&fem_loop_kernel<T, R, MT, kFar>);
   if (lds > 64 * 1024) {
     const hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (ea != hipSuccess) {
@@ -1689,7 +1697,7 @@ static hipError_t resident_fem_loop(const FemLoopArgs<T>& a, size_t lds, int cus
   // nothing else of a cooperative launch (no grid-wide sync object; workgroups exchange
   // through polled buffers whose waits are bounded and report FLAG_BARRIER on expiry), and
   // a cooperative launch would put the dispatch on the runtime's separate cooperative queue.
-  hipLaunchKernelGGL((fem_loop_kernel<T, R, MT>), dim3(a.t.n_sub), dim3(kFemThreads), lds, s, a);
+  hipLaunchKernelGGL((fem_loop_kernel<T, R, MT, kFar>), dim3(a.t.n_sub), dim3(kFemThreads), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1706,9 +1714,9 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
     const hipError_t ze = hipGetLastError();
     if (ze != hipSuccess) return ze;
   }
-  const auto lds_of = [&](int mtw) -> size_t {
+  const auto lds_of = [&](int mtw, bool far = false) -> size_t {
     return sizeof(double) * kFemRed + sizeof(T) * (5 * (size_t)mtw + 8 * (size_t)a.max_ng) +
-           sizeof(int) * 4 * (size_t)a.max_ng + sizeof(T) * ((2 * kRing + 1) * (size_t)a.max_nc + 4) +
+           sizeof(int) * 4 * (size_t)a.max_ng + sizeof(T) * (((far ? 0 : 2 * kRing) + 1) * (size_t)a.max_nc + 4) +
            sizeof(int) * (size_t)mtw + 2 * sizeof(uint16_t) * (size_t)a.max_nc + 16;
   };
   int dev = 0, cus = 0, lds_max = 0;
@@ -1749,6 +1757,8 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
     }
   }
   e = resident_fem_loop<T, 0, 0>(a, lds_of(a.max_mt16), cus, fits, s);
+  if (e != hipSuccess || fits) return e;
+  e = resident_fem_loop<T, 0, 0, true>(a, lds_of(a.max_mt16, true), cus, fits, s);
   if (e != hipSuccess) return e;
   return fits ? hipSuccess : hipErrorCooperativeLaunchTooLarge;
 }

@@ -184,7 +184,7 @@ struct subadmm_problem {
     size_t f_node_off, f_tet_off, f_tet_node, f_pair_off, f_pair_ab, f_pent_off, f_pent, f_node_diag, f_m,
         f_dkey_off, f_perm, f_jtj, f_slot_dk, f_slot_dof, f_dk_off, f_dk_slot, f_if_node0, f_if_node1, f_slot_sgn,
         f_tet_g, f_tet_vol, f_rest, f_mass, f_lame_l, f_lame_m, f_sq_off;
-    size_t fA, fb, fL, fS, fcd, fscr, fe, fvh, fw, fy, fpart, fprec, fkest;
+    size_t fA, fb, fL, fS, fcd, fscr, fe, fvh, fw, fy, fpart, fring, fprec, fkest;
     size_t cl_wg, cl_order, cl_if, cl_bidx, cl_y, cl_part, cl_lost, cl_epoch;
     size_t static_end;
     size_t base;   // end of what every entry point needs (subadmm_solve_scratch holds this much)
@@ -435,6 +435,7 @@ void plan_workspace(subadmm_problem* p) {
     o.fw = real(p->n_slot);
     o.fy = pl.take<unsigned long long>(2 * (p->dtype == SUBADMM_F64 ? kClusterWordsF64 : kClusterWordsF32) * (size_t)p->n_slot);
     o.fpart = pl.take<unsigned long long>(fem_part_words(p->n_sub, p->n_scene));
+    o.fring = real(8 * (size_t)p->n_slot);
     o.fprec = pl.take<int32_t>(p->n_sub);
     o.fkest = pl.take<double>(p->n_sub);
   }
@@ -2565,6 +2566,7 @@ int run_fem_step(subadmm_problem* p, T* pos, T* vel, double dt, int32_t max_iter
   a.ybuf = at<unsigned long long>(p, o.fy);
   a.lambda = lambda;
   a.part = at<unsigned long long>(p, o.fpart);
+  a.ring = at<T>(p, o.fring);
   a.st_iters = at<int32_t>(p, o.st_it);
   a.st_total = at<long long>(p, o.st_tot);
   a.st_unconv = at<long long>(p, o.st_unc);
