@@ -21,6 +21,7 @@
 #include "internal.hpp"
 #include "mfma.hpp"
 #include "rigid_device.hpp"
+#include "row_walk.hpp"
 
 namespace subadmm {
 
@@ -118,29 +119,22 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   const T* J = a.J + a.t.sub_J[i];
   const T* b = a.b + a.t.sub_dof[i];
   if (tid == 0) bad = 0;
-  // t / n for t < 2^20 and quotients below 2^11 (n <= 512): (t + 1/2) / n lies 1 / 2n at least
-  // from a whole number, further than the rounding of the product with the reciprocal
-  const float inv_n = 1.0f / (float)n;
-  auto div_n = [&](int t) { return (int)(((float)t + 0.5f) * inv_n); };
+  const RowWalk first(tid, bd, n);
+  RowWalk e = first;
 #pragma unroll 4
-  for (int t = tid; t < n * n; t += bd) {
-    const int r = div_n(t), c = t - r * n;
-    K[r * ld + c] = (C)A[t];
-  }
+  for (int t = tid; t < n * n; t += bd, e.next()) K[e.row * ld + e.col] = (C)A[t];
+  e = first;
 #pragma unroll 4
-  for (int t = tid; t < nc * n; t += bd) {
-    const int r = div_n(t), c = t - r * n;
-    Jl[r * ld + c] = (C)J[t];
-  }
+  for (int t = tid; t < nc * n; t += bd, e.next()) Jl[e.row * ld + e.col] = (C)J[t];
   for (int t = tid; t < n; t += bd) X[nc * ld + t] = (C)b[t];
   Grp::sync();
 
   // Eq. (23): beta_i = Tr(A_i) / Tr(J^T J); Tr(J^T J) = |J|_F^2.
   double trA = 0.0, trJ = 0.0;
   for (int t = tid; t < n; t += bd) trA += (double)K[t * ld + t];
-  for (int t = tid; t < nc * n; t += bd) {
-    const int r = div_n(t);
-    const C v = Jl[r * ld + t - r * n];
+  e = first;
+  for (int t = tid; t < nc * n; t += bd, e.next()) {
+    const C v = Jl[e.row * ld + e.col];
     trJ = tfma((double)v, (double)v, trJ);
   }
   if constexpr (Grp::kWave) {
@@ -194,14 +188,11 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   }
   Grp::sync();
   // K_hat = S K S, J_hat = J S (S = diag(sc)).
-  for (int t = tid; t < n * n; t += bd) {
-    const int r = div_n(t), c = t - r * n;
-    if (c <= r) K[r * ld + c] *= sc[r] * sc[c];
-  }
-  for (int t = tid; t < (nc + 1) * n; t += bd) {
-    const int r = div_n(t), c = t - r * n;
-    X[r * ld + c] *= sc[c];  // J_hat rows, then S b
-  }
+  e = first;
+  for (int t = tid; t < n * n; t += bd, e.next())
+    if (e.col <= e.row) K[e.row * ld + e.col] *= sc[e.row] * sc[e.col];
+  e = first;
+  for (int t = tid; t < (nc + 1) * n; t += bd, e.next()) X[e.row * ld + e.col] *= sc[e.col];  // J_hat rows, then S b
   Grp::sync();
 
   // Cholesky factor L of K_hat, 16 columns at a time; diagonal tiles hold their inverses.
