@@ -1614,8 +1614,7 @@ hipError_t launch_loop(const LoopArgs<T>& a, int max_slot_scene, int max_if_scen
 // The phases read their arguments through the argument block in device memory, and the
 // block's address passes through an empty asm statement at the start of each phase: the
 // compiler cannot move a phase's argument loads into another phase, so no phase keeps the
-// others' arguments live in registers (the whole kernel inlined, its LDS addressed
-// directly).
+// others' arguments live in registers.
 template <typename T>
 __device__ __attribute__((always_inline)) inline const StepsArgs<T>* phase_args(const StepsArgs<T>* p) {
   uint64_t v = reinterpret_cast<uint64_t>(p);
@@ -1623,9 +1622,13 @@ __device__ __attribute__((always_inline)) inline const StepsArgs<T>* phase_args(
   return reinterpret_cast<const StepsArgs<T>*>(v);
 }
 
-// The factorisations called out of line: inlined, their registers (the diagonal tiles' rows) cost
-// the iteration spills (512 legged scenes, two steps: 3.55 ms before the matrix-core form, 3.71
-// with it inlined).  The LDS area is passed as its LDS offset, so that it is addressed directly.
+// The factorisations and the iteration called out of line, so that each has its own registers:
+// with the factorisations inlined their diagonal tiles' rows cost the iteration spills (512 legged
+// scenes, two steps: 3.55 ms before the matrix-core form, 3.71 with it inlined), and with the
+// iteration inlined beside the calls it read 5 to 9 spilled registers per iteration in FP64 and
+// any change of a factorisation moved its spills (FP64 chain of 8 links, 100 steps: 345 us a step
+// before the matrix-core factorisation, 356 with the iteration inlined, 288 now; FP32 240 either
+// way).  The LDS area is passed as its LDS offset, so that it is addressed directly.
 template <typename T, typename C>
 __device__ __attribute__((noinline)) void factor_wave_outlined(const FactorArgs<T>& a, const int i, const uint32_t lds) {
   __shared__ int bad[4];
@@ -1644,10 +1647,15 @@ __device__ __attribute__((noinline)) void factor_global_outlined(const FactorArg
   factor_body<T, C, GroupWg>(a, i, scr, red, bad);
 }
 
+template <typename T, int kLanes>
+__device__ __attribute__((noinline)) void loop_outlined(const LoopArgs<T>& a, const int sc, const uint32_t lds) {
+  __shared__ __align__(16) T red[2][8];
+  loop_body<T, kHLds, kLanes>(a, sc, (unsigned char*)(__attribute__((address_space(3))) unsigned char*)lds, red);
+}
+
 template <typename T, typename C, int kLanes>
 __global__ void __launch_bounds__(256, 4) steps_kernel(const StepsArgs<T>* __restrict__ ap) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ __align__(16) T lred[2][8];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw;
   // workgroups are dispatched round-robin over the XCDs and their CUs in block order, so the
   // order decides which scenes share a CU
@@ -1689,7 +1697,7 @@ __global__ void __launch_bounds__(256, 4) steps_kernel(const StepsArgs<T>* __res
       }
     }
     // the iteration (Eq. 15-22, 14) from the previous step's values or cold
-    loop_body<T, kHLds, kLanes>(phase_args(ap)->l, sc, smem_raw, lred);
+    loop_outlined<T, kLanes>(phase_args(ap)->l, sc, lds0);
     __syncthreads();
     {
       // state update (Eq. 2)
