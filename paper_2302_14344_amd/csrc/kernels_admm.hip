@@ -741,8 +741,9 @@ __device__ inline T row_dot_share(const VT* Hv, const VT* Wv, int cnt, int hs, i
 
 // The whole iteration of scene sc by the workgroup; smem_raw is the dynamic LDS area, red a
 // workgroup-shared scratch for the residual sums.  kMulti: the problem has interfaces of more
-// than two members (a form of its own, so that the others do not carry its registers).
-template <typename T, int kHMode, int kLanes, bool kMulti = false>
+// than two members (a form of its own, so that the others do not carry its registers).  kOutlined:
+// called from the multi-step kernel.
+template <typename T, int kHMode, int kLanes, bool kMulti = false, bool kOutlined = false>
 __device__ __attribute__((always_inline)) inline void loop_body(const LoopArgs<T>& a, const int sc,
                                                                unsigned char* smem_raw, T (*red)[8]) {
   static_assert(kLanes > 0 || kHMode == 1, "split rows need the LDS layout");
@@ -999,6 +1000,8 @@ __device__ __attribute__((always_inline)) inline void loop_body(const LoopArgs<T
       }
       // equality and soft: lambda = p; hard inequality: max(0, p); contact: Eq. (21)
       T cl[3];
+      // written here, so that it is not carried from one iteration to the next in three registers
+      if constexpr (kOutlined) cl[0] = cl[1] = cl[2] = (T)0;
       contact_project<T>(p, mu, cl, a.contact_model);
 #pragma unroll
       for (int k = 0; k < kMaxIfDim; ++k) {
@@ -1627,8 +1630,8 @@ __device__ __attribute__((always_inline)) inline const StepsArgs<T>* phase_args(
 // scenes, two steps: 3.55 ms before the matrix-core form, 3.71 with it inlined), and with the
 // iteration inlined beside the calls it read 5 to 9 spilled registers per iteration in FP64 and
 // any change of a factorisation moved its spills (FP64 chain of 8 links, 100 steps: 345 us a step
-// before the matrix-core factorisation, 356 with the iteration inlined, 288 now; FP32 240 either
-// way).  The LDS area is passed as its LDS offset, so that it is addressed directly.
+// before the matrix-core factorisation, 356 with the iteration inlined, 290 now; FP32 240 either
+// way, two steps of 512 legged scenes 3.32 ms either way).  The LDS area is passed as its LDS offset, so that it is addressed directly.
 template <typename T, typename C>
 __device__ __attribute__((noinline)) void factor_wave_outlined(const FactorArgs<T>& a, const int i, const uint32_t lds) {
   __shared__ int bad[4];
@@ -1650,7 +1653,7 @@ __device__ __attribute__((noinline)) void factor_global_outlined(const FactorArg
 template <typename T, int kLanes>
 __device__ __attribute__((noinline)) void loop_outlined(const LoopArgs<T>& a, const int sc, const uint32_t lds) {
   __shared__ __align__(16) T red[2][8];
-  loop_body<T, kHLds, kLanes>(a, sc, (unsigned char*)(__attribute__((address_space(3))) unsigned char*)lds, red);
+  loop_body<T, kHLds, kLanes, false, true>(a, sc, (unsigned char*)(__attribute__((address_space(3))) unsigned char*)lds, red);
 }
 
 template <typename T, typename C, int kLanes>
