@@ -93,7 +93,10 @@ __device__ inline C tile_at(P p, int i, bool in) {
 // sides, H = T^T T, and the block back substitution.  A wave owns 16 right-hand sides from
 // start to end, so the substitutions have no barrier; the group synchronises three times per
 // 16 columns of the factor.  A tile's arithmetic does not depend on which wave forms it, so
-// the workgroup and the wave form agree except in the trace sums' grouping of Eq. 23.
+// the workgroup and the wave form agree except in the trace sums' grouping of Eq. 23.  Products are
+// subtracted from the entry itself, the accumulator starting from it (added up first, their sum
+// stays at the entry's size while the remainder shrinks, and multipliers of 300-DOF subsystems
+// were 1.9 times as far from the exact ones).
 //
 // Bound by latency: the diagonal tiles (~2.7 us each, one wave) and chains of tile products; few
 // subsystems leave the matrix cores mostly idle.  Measured against the column-by-column form
@@ -199,10 +202,15 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
   for (int p = 0; p < nt; ++p) {
     const int p0 = 16 * p, jb = n - p0 < 16 ? n - p0 : 16;
     if (p > 0) {
-      // U_Ip = K_Ip - sum_{k < p} L_Ik L_pk^T: the lane holds U[cn][row(q, g)]
+      // -U_Ip = -K_Ip + sum_{k < p} L_Ik L_pk^T: the lane holds U[cn][row(q, g)]
       for (int I = p + wv; I < nt; I += nwv) {
         const int ri = 16 * I + cn;
-        MV acc = {0, 0, 0, 0};
+        MV acc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = p0 + M::k(q, g);
+          acc[q] = -tile_at<C>(K, ri * ld + c, ri < n && c < n && c <= ri);
+        }
 #pragma unroll kUnroll
         for (int k0 = 0; k0 < p0; k0 += 16) {
           C av[4], bv[4];
@@ -217,7 +225,7 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int c = p0 + M::k(q, g);
-          if (ri < n && c < n && c <= ri) K[ri * ld + c] -= acc[q];
+          if (ri < n && c < n && c <= ri) K[ri * ld + c] = -acc[q];
         }
       }
       Grp::sync();
@@ -263,7 +271,14 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
     P x = X + (c < m ? c : 0) * ld;
     for (int I = 0; I < nt; ++I) {
       const int i0 = 16 * I, ri = i0 + cn;
-      MV acc = {0, 0, 0, 0};
+      MV acc;
+      C lv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = M::k(q, g);
+        acc[q] = -tile_at<C>(x, i0 + k, c < m && i0 + k < n);
+        lv[q] = tile_at<C>(K, ri * ld + i0 + k, k <= cn && ri < n);
+      }
 #pragma unroll kUnroll
       for (int k0 = 0; k0 < i0; k0 += 16) {
         C av[4], bv[4];
@@ -275,16 +290,11 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
         }
         acc = M::mul(av, bv, acc);
       }
-      C av[4], bv[4];
+      C bv[4];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = M::k(s, g);
-        av[s] = tile_at<C>(K, ri * ld + i0 + k, k <= cn && ri < n);
-        const bool in = c < m && i0 + k < n;
-        bv[s] = in ? tile_at<C>(x, i0 + k, in) - acc[s] : (C)0;
-      }
+      for (int s = 0; s < 4; ++s) bv[s] = -acc[s];
       MV out = {0, 0, 0, 0};
-      out = M::mul(av, bv, out);
+      out = M::mul(lv, bv, out);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int r = i0 + M::k(q, g);
@@ -330,7 +340,14 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
     P x = X + (c < m ? c : 0) * ld;
     for (int I = nt - 1; I >= 0; --I) {
       const int i0 = 16 * I;
-      MV acc = {0, 0, 0, 0};
+      MV acc;
+      C lv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = M::k(q, g);
+        acc[q] = -tile_at<C>(x, i0 + k, c < m && i0 + k < n);
+        lv[q] = tile_at<C>(K, (i0 + k) * ld + i0 + cn, cn <= k && i0 + k < n);
+      }
 #pragma unroll kUnroll
       for (int k0 = i0 + 16; k0 < n; k0 += 16) {
         C av[4], bv[4];
@@ -342,16 +359,11 @@ __device__ __attribute__((always_inline)) inline void factor_body(const FactorAr
         }
         acc = M::mul(av, bv, acc);
       }
-      C av[4], bv[4];
+      C bv[4];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = M::k(s, g);
-        av[s] = tile_at<C>(K, (i0 + k) * ld + i0 + cn, cn <= k && i0 + k < n);
-        const bool in = c < m && i0 + k < n;
-        bv[s] = in ? tile_at<C>(x, i0 + k, in) - acc[s] : (C)0;
-      }
+      for (int s = 0; s < 4; ++s) bv[s] = -acc[s];
       MV out = {0, 0, 0, 0};
-      out = M::mul(av, bv, out);
+      out = M::mul(lv, bv, out);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int r = i0 + M::k(q, g);
