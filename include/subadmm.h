@@ -206,9 +206,10 @@ enum subadmm_option {
    * between the phases), larger ones with one launch per phase of each iteration over all
    * scenes (x-update per slot row, residual and stopping test per scene, z-update per
    * interface), where eager steps stop launching once every scene has stopped (checked
-   * every 32 iterations).  All forms compute the same iteration bit for bit; scenes stop
-   * independently.  The learned start and subadmm_rigid_steps need the
-   * per-scene kernel. */
+   * every 32 iterations).  In all forms every row and interface rounds alike, bit for bit;
+   * the form with several workgroups per scene sums the residual by workgroups, so there a
+   * scene at its tolerance may stop at another iteration than in the other two.  Scenes stop
+   * independently.  The learned start and subadmm_rigid_steps need the per-scene kernel. */
   SUBADMM_OPT_LARGE_PATH = 8,
   /* 1 = after every solve and rigid step (subadmm_solve, subadmm_solve_scratch,
    * subadmm_rigid_step, its graph form, and the last step of subadmm_rigid_steps) one

@@ -1747,8 +1747,9 @@ __global__ void __launch_bounds__(256) large_init_kernel(LargeArgs<T> a) {
   a.u[g] = u0;
 }
 
-// x-update of slot row g (Eq. 15 reassociated, y = beta x + u) with its residual terms
-template <typename T>
+// x-update of slot row g (Eq. 15 reassociated, y = beta x + u) with its residual terms (kSquare
+// false: the terms before they are squared)
+template <typename T, bool kSquare = true>
 __device__ inline void large_xupdate_row(const LargeArgs<T>& a, const long g) {
   const LoopArgs<T>& l = a.l;
   const int i = l.t.slot_sub[g];
@@ -1765,8 +1766,8 @@ __device__ inline void large_xupdate_row(const LargeArgs<T>& a, const long g) {
   const T x = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   const T yn = l.beta[i] * (l.d[g] + x) + a.u[g];
   const double df = (double)yn - (double)a.y[g];
-  a.dy2[g] = df * df;
-  a.yy2[g] = (double)yn * (double)yn;
+  a.dy2[g] = kSquare ? df * df : df;
+  a.yy2[g] = kSquare ? (double)yn * (double)yn : (double)yn;
   a.y[g] = yn;
 }
 
@@ -1778,13 +1779,12 @@ __global__ void __launch_bounds__(256) large_xupdate_kernel(LargeArgs<T> a) {
   large_xupdate_row<T>(a, g);
 }
 
-// The stopping test of scene sc from its wave partials (fixed order); writes the statistics
-// and the scene's stop flag; returns whether the scene stopped.
+// The stopping test of scene sc from its sums of Eq. 22; writes the statistics and the scene's
+// stop flag; returns whether the scene stopped.
 template <typename T>
-__device__ inline int large_decide(const LargeArgs<T>& a, const int sc, const int l_iter, double (*red)[4]) {
+__device__ inline int large_decide(const LargeArgs<T>& a, const int sc, const int l_iter, const double th,
+                                   const double yy) {
   const LoopArgs<T>& l = a.l;
-  const double th = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-  const double yy = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
   const int it = l_iter + 1;
   const bool bad = !__builtin_isfinite(th) || !__builtin_isfinite(yy);
   const bool cv = !bad && th <= l.tol * l.tol * (yy > 1e-24 ? yy : 1e-24);
@@ -1827,7 +1827,9 @@ __device__ inline bool large_residual_scene(const LargeArgs<T>& a, const int sc,
     }
   }
   __syncthreads();
-  if (tid == 0) *stop = large_decide<T>(a, sc, l_iter, red);
+  if (tid == 0)
+    *stop = large_decide<T>(a, sc, l_iter, (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
+                            (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
   __syncthreads();
   return *stop != 0;
 }
@@ -1935,18 +1937,19 @@ __global__ void __launch_bounds__(256) large_final_kernel(LargeArgs<T> a) {
 // beyond the per-scene kernel's LDS layout but whose iteration one workgroup carries well):
 // the same per-row x-update, per-scene residual (same summation order) and per-interface
 // z-update as the phase kernels, with workgroup barriers in place of kernel boundaries, on
-// the same global slot arrays.  Bitwise equal to the phase kernels.
-template <typename T>
-__device__ inline void large_scene_iterate(const LargeArgs<T>& a, const int sc, double (*red)[4], int* stop) {
+// the same global slot arrays.  Bitwise equal to the phase kernels.  residual(it): the stopping
+// test of iteration it, from terms that are squared as kSquare says.
+template <typename T, bool kSquare, typename R>
+__device__ inline void large_scene_iterate(const LargeArgs<T>& a, const int sc, R&& residual) {
   const LoopArgs<T>& l = a.l;
   const int tid = threadIdx.x, bd = blockDim.x;
   const int s0 = l.t.sc_slot[sc], s1 = l.t.sc_slot[sc + 1];
   const int i0 = l.t.sc_if[sc], i1 = l.t.sc_if[sc + 1];
   const int d0 = l.t.sc_dof[sc], d1 = l.t.sc_dof[sc + 1];
   for (int it = 0; it < l.max_iters; ++it) {
-    for (int g = s0 + tid; g < s1; g += bd) large_xupdate_row<T>(a, g);
+    for (int g = s0 + tid; g < s1; g += bd) large_xupdate_row<T, kSquare>(a, g);
     __syncthreads();
-    if (large_residual_scene<T>(a, sc, it, red, stop)) break;
+    if (residual(it)) break;
     for (int j = i0 + tid; j < i1; j += bd) large_zupdate_if<T>(a, j);
     __syncthreads();
   }
@@ -1972,7 +1975,7 @@ __global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
     a.u[g] = u0;
   }
   __syncthreads();
-  large_scene_iterate<T>(a, sc, red, &stop);
+  large_scene_iterate<T, true>(a, sc, [&](int it) { return large_residual_scene<T>(a, sc, it, red, &stop); });
 }
 
 // ------------------------------------------------------------------------------------
@@ -1995,7 +1998,8 @@ __global__ void __launch_bounds__(1024) large_scene_kernel(LargeArgs<T> a) {
 // every wait is bounded: when it expires the workgroup marks the scene lost and leaves, and
 // the tail kernel runs that scene again from its start values (kept in y, u, w) with one
 // workgroup.  Per-row and per-interface arithmetic and its order are those of the phase
-// kernels, so v_hat, lambda, z and u are the same bits.
+// kernels, so v_hat, lambda, z and u of an iteration are the same bits.  The residual is summed by
+// lanes, waves and workgroups, in the tail kernel too: what a wait that expires changes is the time.
 //
 // Bound by latency: one exchange through the coherent point and the three workgroup barriers
 // around it per iteration, ~2.7 us, against the phase kernels' three launches (~20 us) or one
@@ -2283,8 +2287,8 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_scene_kernel(ClusterA
         const T yn = be[p] * (dr[p] + x) + uo;
         if (bx[p] >= 0) X::put(yb + bx[p], yn, tag);
         const double df = (double)yn - (double)yo;
-        pth = df * df + pth;
-        pyy = (double)yn * (double)yn + pyy;
+        pth = __builtin_fma(df, df, pth);
+        pyy = __builtin_fma((double)yn, (double)yn, pyy);
         y[r] = yn;
       }
     }
@@ -2462,18 +2466,76 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_scene_kernel(ClusterA
   }
 }
 
+// Residual of Eq. 22 of scene sc by one workgroup in the order of the scene's workgroups `first` to
+// first + count - 1 in cluster_scene_kernel (its rows per lane, lanes, waves, workgroups), so that a
+// scene that is run again stops at the iteration where it would have, and the stopping test.
+template <typename T>
+__device__ inline bool cluster_residual_scene(const ClusterArgs<T>& a, const int sc, const int first, const int count,
+                                              const int l_iter, double (*part)[kClusterThreads], double (*pred)[8],
+                                              int* stop) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
+  const int32_t* sub_slot = a.g.l.t.sub_slot;
+  for (int m = wv; m < count; m += nwv) {
+    const int32_t* dsc = a.wg + 8 * (long)(first + m);
+    const int s0 = sub_slot[dsc[1]], ns = sub_slot[dsc[2]] - s0;
+    double sth = 0.0, syy = 0.0;
+    for (int q = 0; q < kClusterThreads / 64 && 64 * q < ns; ++q) {
+      double pth = 0.0, pyy = 0.0;
+      for (int r = 64 * q + lane; r < ns; r += kClusterThreads) {
+        const double df = a.g.dy2[s0 + r], yn = a.g.yy2[s0 + r];
+        pth = __builtin_fma(df, df, pth);
+        pyy = __builtin_fma(yn, yn, pyy);
+      }
+      sth += wave_total_lane63(pth);
+      syy += wave_total_lane63(pyy);
+    }
+    if (lane == 63) {
+      part[0][m] = sth;
+      part[1][m] = syy;
+    }
+  }
+  __syncthreads();
+  const int npw = (count + 63) / 64;
+  for (int q = wv; q < npw; q += nwv) {
+    const int m = 64 * q + lane;
+    const double sth = wave_total_lane63(m < count ? part[0][m] : 0.0);
+    const double syy = wave_total_lane63(m < count ? part[1][m] : 0.0);
+    if (lane == 63) {
+      pred[0][q] = sth;
+      pred[1][q] = syy;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double th = pred[0][0], yy = pred[1][0];
+    for (int q = 1; q < npw; ++q) {
+      th += pred[0][q];
+      yy += pred[1][q];
+    }
+    *stop = large_decide<T>(a.g, sc, l_iter, th, yy);
+  }
+  __syncthreads();
+  return *stop != 0;
+}
+
 // After the cluster kernel, one workgroup per scene: the totals of a scene that ran through,
 // or the whole iteration of one whose waits expired; then the tags of the next launch.
 template <typename T>
 __global__ void __launch_bounds__(1024) cluster_tail_kernel(ClusterArgs<T> a) {
-  __shared__ double red[2][4];
-  __shared__ int stop;
+  __shared__ double part[2][kClusterThreads];
+  __shared__ double pred[2][8];
+  __shared__ int stop, s_first;
   const int sc = blockIdx.x;
   if (sc == 0 && threadIdx.x == 0) *a.epoch += (uint32_t)a.g.l.max_iters + 1u;
   if (a.lost[sc]) {
+    for (int m = threadIdx.x; m < a.n_wg; m += blockDim.x)
+      if (a.wg[8 * (long)m] == sc) s_first = a.wg[8 * (long)m + 5];
     __syncthreads();
     if (threadIdx.x == 0) a.lost[sc] = 0;
-    large_scene_iterate<T>(a.g, sc, red, &stop);
+    const int first = s_first, count = a.wg[8 * (long)first + 6];
+    large_scene_iterate<T, false>(a.g, sc, [&](int it) {
+      return cluster_residual_scene<T>(a, sc, first, count, it, part, pred, &stop);
+    });
   } else if (threadIdx.x == 0) {
     a.g.l.st_total[sc] += a.g.l.st_iters[sc];
     if (!a.g.l.st_conv[sc]) a.g.l.st_unconv[sc] += 1;

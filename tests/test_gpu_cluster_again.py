@@ -1,0 +1,62 @@
+"""A large scene that a workgroup gave up waiting for is solved again by one workgroup: the sums of
+the stopping test are formed in the same order there, so the statistics are the same bits and the scene
+stops at the same iteration, also where the tolerance is the residual of an iteration itself.
+
+Sizes: one and two slot rows per thread, register and LDS forms, scenes of one to several
+workgroups.  The wait of zero ticks gives a scene up at the first value that is not there yet.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2302_14344_amd import scenes as S
+
+pytestmark = pytest.mark.gpu
+
+CASES = {  # scenes, subsystems, interfaces, DOF, seed
+    "nc27": (3, (180, 200), (220, 230), (3, 12), 8),
+    "nc51": (2, (60, 70), (190, 220), (3, 12), 2),
+    "wide": (1, (12, 12), (150, 150), (3, 12), 4),
+    "two-rows": (90, (60, 66), (170, 180), (3, 6), 11),
+}
+
+
+def _wait(pr, ticks):
+    from paper_2302_14344_amd import _lib as L
+    fn = L.lib().subadmm_large_scene_wait
+    fn.argtypes, fn.restype = [C.c_void_p, C.c_longlong], C.c_int
+    return fn(pr._h, ticks)
+
+
+def _solve(pr, p, iters, tol, ticks):
+    assert _wait(pr, ticks) > 0
+    o = pr.solve(pr.tensor(p.A), pr.tensor(p.b), pr.tensor(p.J), pr.tensor(p.e), max_iters=iters, tol=tol)
+    st = pr.stats()
+    pr.check()
+    return {k: o[k].cpu().numpy() for k in ("v_hat", "lam", "z", "u")}, st
+
+
+def _problem(case):
+    n, subs, ifs, ndof, seed = CASES[case]
+    return S.random_assembled(seed, n_scenes=n, subs_per_scene=subs, ndof=ndof, n_if_per_scene=ifs,
+                              kinds=(0, 1, 2, 3), eq_dim=(1, 6))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("case", list(CASES))
+def test_stops_where_it_would_have(case, dtype):
+    from paper_2302_14344_amd.solver import Problem
+    print(case, dtype, flush=True)
+    p = _problem(case)
+    pr = Problem.from_assembled(p, dtype=dtype)
+    _, st = _solve(pr, p, 20, 0.0, -1)
+    # the residual of the 20th iteration of each scene in turn, as the tolerance
+    for tol in [0.0, *st["r_theta"][:3]]:
+        a, sa = _solve(pr, p, 40, float(tol), -1)
+        b, sb = _solve(pr, p, 40, float(tol), 0)
+        for k in ("iters", "converged", "theta", "r_theta"):
+            np.testing.assert_array_equal(sa[k], sb[k], err_msg=k)
+        for k in a:
+            np.testing.assert_array_equal(a[k], b[k], err_msg=k)
