@@ -208,8 +208,15 @@ enum subadmm_option {
    * interface), where eager steps stop launching once every scene has stopped (checked
    * every 32 iterations).  In all forms every row and interface rounds alike, bit for bit;
    * the form with several workgroups per scene sums the residual by workgroups, so there a
-   * scene at its tolerance may stop at another iteration than in the other two.  Scenes stop
-   * independently.  The learned start and subadmm_rigid_steps need the per-scene kernel. */
+   * scene at its tolerance may stop at another iteration than in the other two.  That form
+   * takes at most 256 workgroups in all, of at most 1,024 slot rows and 512 interfaces each
+   * (256 scenes of up to 1,024 rows or 128 of up to 2,048; larger batches take the other
+   * forms), and needs them on the device together: beside kernels of other streams that hold
+   * compute units it waits for these to end (30 iterations of a scene of 6.5k rows beside a
+   * kernel that holds 240 units for 13.7 ms: 12.1 ms, alone 0.16; with value 1 or 2 0.67 in
+   * both cases).  Programs that overlap long kernels on several streams choose 1 or 2.  A
+   * wait of more than 20 ms ends in the scene being solved again by one workgroup.  Scenes
+   * stop independently.  The learned start and subadmm_rigid_steps need the per-scene kernel. */
   SUBADMM_OPT_LARGE_PATH = 8,
   /* 1 = after every solve and rigid step (subadmm_solve, subadmm_solve_scratch,
    * subadmm_rigid_step, its graph form, and the last step of subadmm_rigid_steps) one

@@ -60,3 +60,35 @@ def test_stops_where_it_would_have(case, dtype):
             np.testing.assert_array_equal(sa[k], sb[k], err_msg=k)
         for k in a:
             np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+def test_beside_a_kernel_that_holds_the_device():
+    """A large scene on a second stream while a solve of ~27 ms holds most CUs: its workgroups are not
+    all resident and waits of 20 ms may expire; the result is that of the scene alone."""
+    from paper_2302_14344_amd.solver import Problem
+    hold = S.random_assembled(5, n_scenes=240, subs_per_scene=(24, 24), ndof=(6, 12), n_if_per_scene=(75, 75),
+                              kinds=(0, 1), eq_dim=(3, 3))
+    p = S.random_assembled(8, n_scenes=1, subs_per_scene=(400, 400), ndof=(3, 12), n_if_per_scene=(1200, 1200),
+                           kinds=(0, 1, 2, 3), eq_dim=(1, 6))
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(one):
+        ph = Problem.from_assembled(hold, dtype=torch.float32)
+        ah = [ph.tensor(x) for x in (hold.A, hold.b, hold.J, hold.e)]
+        ph.solve(*ah, max_iters=10, tol=0.0)
+    with torch.cuda.stream(two):
+        pr = Problem.from_assembled(p, dtype=torch.float32)
+        assert _wait(pr, -1) > 256 - 240
+        a = [pr.tensor(x) for x in (p.A, p.b, p.J, p.e)]
+        alone = pr.solve(*a, max_iters=30, tol=0.0)
+        alone_st = pr.stats()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(one):
+        ph.solve(*ah, max_iters=20000, tol=0.0)
+    with torch.cuda.stream(two):
+        both = pr.solve(*a, max_iters=30, tol=0.0)
+        both_st = pr.stats()
+        pr.check()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(alone_st["theta"], both_st["theta"])
+    for k in alone:
+        np.testing.assert_array_equal(alone[k].cpu().numpy(), both[k].cpu().numpy(), err_msg=k)
