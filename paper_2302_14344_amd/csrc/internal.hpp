@@ -230,6 +230,7 @@ struct ClusterArgs {
   unsigned long long* ybuf;  // 2 x n_ex values: y of the exchanged rows by iteration parity
   unsigned long long* part;  // 2 x n_wg x 4 words: residual partials
   int32_t* lost;             // per scene: a wait expired
+  int32_t* again;            // scenes solved again by the tail kernel since the bind
   uint32_t* epoch;           // tag base of this launch
   long long wait_ticks;      // longest wait, in ticks of the 100 MHz clock
   int64_t n_ex;

@@ -2531,7 +2531,10 @@ __global__ void __launch_bounds__(1024) cluster_tail_kernel(ClusterArgs<T> a) {
     for (int m = threadIdx.x; m < a.n_wg; m += blockDim.x)
       if (a.wg[8 * (long)m] == sc) s_first = a.wg[8 * (long)m + 5];
     __syncthreads();
-    if (threadIdx.x == 0) a.lost[sc] = 0;
+    if (threadIdx.x == 0) {
+      a.lost[sc] = 0;
+      atomicAdd(a.again, 1);
+    }
     const int first = s_first, count = a.wg[8 * (long)first + 6];
     large_scene_iterate<T, false>(a.g, sc, [&](int it) {
       return cluster_residual_scene<T>(a, sc, first, count, it, part, pred, &stop);

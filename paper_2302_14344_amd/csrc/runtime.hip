@@ -185,7 +185,7 @@ struct subadmm_problem {
         f_dkey_off, f_perm, f_jtj, f_slot_dk, f_slot_dof, f_dk_off, f_dk_slot, f_if_node0, f_if_node1, f_slot_sgn,
         f_tet_g, f_tet_vol, f_rest, f_mass, f_lame_l, f_lame_m, f_sq_off;
     size_t fA, fb, fL, fS, fcd, fscr, fe, fvh, fw, fy, fpart, fring, fprec, fkest;
-    size_t cl_wg, cl_order, cl_if, cl_bidx, cl_y, cl_part, cl_lost, cl_epoch;
+    size_t cl_wg, cl_order, cl_if, cl_bidx, cl_y, cl_part, cl_lost, cl_again, cl_epoch;
     size_t static_end;
     size_t base;   // end of what every entry point needs (subadmm_solve_scratch holds this much)
     size_t total;
@@ -450,6 +450,7 @@ void plan_workspace(subadmm_problem* p) {
     o.cl_y = pl.take<unsigned long long>(2 * words * (size_t)p->cl_nex);
     o.cl_part = pl.take<unsigned long long>(p->cl_wg.size());  // 2 x 4 words per workgroup
     o.cl_lost = pl.take<int32_t>(p->n_scene);
+    o.cl_again = pl.take<int32_t>(1);
     o.cl_epoch = pl.take<uint32_t>(1);
   }
   o.total = (pl.off + 255) & ~size_t(255);
@@ -853,6 +854,7 @@ int run_loop(subadmm_problem* p, const T* e, int32_t max_iters, double tol, cons
       ca.ybuf = at<unsigned long long>(p, o.cl_y);
       ca.part = at<unsigned long long>(p, o.cl_part);
       ca.lost = at<int32_t>(p, o.cl_lost);
+      ca.again = at<int32_t>(p, o.cl_again);
       ca.epoch = at<uint32_t>(p, o.cl_epoch);
       ca.wait_ticks = p->cl_wait;
       ca.n_ex = p->cl_nex;
@@ -1808,6 +1810,16 @@ SUBADMM_API int subadmm_large_scene_wait(subadmm_problem* p, long long ticks) {
   p->cl_wait = ticks < 0 ? kClusterWait : ticks;
   ++p->cfg_gen;
   return p->cl_fits ? (int)(p->cl_wg.size() / 8) : 0;
+}
+
+// For tests (not in the header): how many scenes were given up and solved again by the tail kernel
+// since the bind (-1: the problem's scenes are not in this form).  Waits for the stream.
+SUBADMM_API int subadmm_large_scene_again(subadmm_problem* p) {
+  if (!p || !p->cl_fits || !p->bound) return -1;
+  int32_t n = -1;
+  hipError_t e = hipMemcpyAsync(&n, at<int32_t>(p, p->o.cl_again), sizeof n, hipMemcpyDeviceToHost, p->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+  return e == hipSuccess ? n : -1;
 }
 
 SUBADMM_API int subadmm_solve(subadmm_problem* p, const void* A, const void* b, const void* J, const void* e,

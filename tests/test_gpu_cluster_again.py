@@ -30,6 +30,13 @@ def _wait(pr, ticks):
     return fn(pr._h, ticks)
 
 
+def _again(pr):
+    from paper_2302_14344_amd import _lib as L
+    fn = L.lib().subadmm_large_scene_again
+    fn.argtypes, fn.restype = [C.c_void_p], C.c_int
+    return fn(pr._h)
+
+
 def _solve(pr, p, iters, tol, ticks):
     assert _wait(pr, ticks) > 0
     o = pr.solve(pr.tensor(p.A), pr.tensor(p.b), pr.tensor(p.J), pr.tensor(p.e), max_iters=iters, tol=tol)
@@ -60,6 +67,22 @@ def test_stops_where_it_would_have(case, dtype):
             np.testing.assert_array_equal(sa[k], sb[k], err_msg=k)
         for k in a:
             np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_scenes_given_up_are_counted(dtype):
+    """A wait of zero ticks gives scenes up (which the equal results alone would not show), ordinary
+    waits give none up."""
+    from paper_2302_14344_amd.solver import Problem
+    p = _problem("nc51")
+    pr = Problem.from_assembled(p, dtype=dtype)
+    _solve(pr, p, 40, 0.0, -1)
+    assert _again(pr) == 0
+    _solve(pr, p, 40, 0.0, 0)
+    n = _again(pr)
+    assert 1 <= n <= 2
+    _solve(pr, p, 40, 0.0, -1)
+    assert _again(pr) == n
 
 
 def test_beside_a_kernel_that_holds_the_device():
