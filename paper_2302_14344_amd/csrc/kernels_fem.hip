@@ -1164,7 +1164,8 @@ constexpr int kFemRed = 20;  // doubles: own partial (4 waves x 2), scene's sum 
 //
 // Workgroups per CU, which bound the number of blocks of a launch: two of the resident form, three
 // or four of the others (the registers are held to that).  kFar: the ring in device memory, for
-// the launches whose blocks would not all be resident with it in LDS (large FP64 blocks in numbers).
+// the launches whose blocks would not all be resident with it in LDS (blocks of more than ~415 slot
+// rows beside LDS tiles, large FP64 blocks in numbers).
 template <typename T, int R, int MT, bool kFar = false>
 __global__ void __launch_bounds__(kFemThreads, R > 0 ? 2 : MT == 0 ? (sizeof(T) == 8 ? 2 : 3) : MT <= 12 ? 4 : 3)
     fem_loop_kernel(FemLoopArgs<T> a) {
@@ -1738,11 +1739,21 @@ hipError_t launch_fem_loop(const FemLoopArgs<T>& a, int* form, hipStream_t s) {
       auto run = [&](auto mtc) -> hipError_t {
         constexpr int M = decltype(mtc)::value;
         if (a.resident) {
-          const size_t lds_r = lds_of(16 * M) + (size_t)lds_tiles_before(M, kResTiles, 4) * 256 * sizeof(T);
-          if (lds_r <= (size_t)lds_max) {
-            const hipError_t er = resident_fem_loop<T, kResTiles, M>(a, lds_r, cus, fits, s);
+          constexpr size_t tiles = (size_t)lds_tiles_before(M, kResTiles, 4) * 256 * sizeof(T);
+          if (lds_of(16 * M) + tiles <= (size_t)lds_max) {
+            const hipError_t er = resident_fem_loop<T, kResTiles, M>(a, lds_of(16 * M) + tiles, cus, fits, s);
             if (fits) *form = kResTiles;
             if (er != hipSuccess || fits) return er;
+          }
+          // operators partly in LDS: beside them the ring leaves room for two blocks a CU up to ~415
+          // slot rows (289 blocks of 300 DOFs, 462 rows: 5.5 us an iteration with the ring in
+          // device memory, 11.1 streaming the operators instead)
+          if constexpr (tiles > 0) {
+            if (lds_of(16 * M, true) + tiles <= (size_t)lds_max) {
+              const hipError_t er = resident_fem_loop<T, kResTiles, M, true>(a, lds_of(16 * M, true) + tiles, cus, fits, s);
+              if (fits) *form = kResTiles;
+              if (er != hipSuccess || fits) return er;
+            }
           }
         }
         return resident_fem_loop<T, 0, M>(a, lds_of(16 * M), cus, fits, s);

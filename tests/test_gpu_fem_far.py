@@ -4,7 +4,9 @@ LDS.  Every form of the operator product rounds alike, so v_hat, lambda, z, u an
 are the same bits, from a cold and a warm start, stopped by the limit at 1, 2, 3 and 7
 iterations and by the tolerance.
 
-* FP64 and FP32, operators streamed: many bodies of nine blocks in one launch, more blocks than the
+* FP32, operators on chip: 289 blocks of 2 x 2 x 25 nodes (up to 462 slot rows, two blocks a CU)
+  against the streamed operators.
+* FP64 and FP32, operators streamed: many bodies of nine such blocks in one launch, more blocks than the
   device holds with the ring in LDS, against the two halves of them in a launch each.
 """
 import numpy as np
@@ -67,6 +69,17 @@ def _run(fs, dtype, tol=None, resident=None, form=None):
         out.append(([_np(x) for x in (vh, lam, *pr.get_warm())], st["iters"], st["theta"], st["converged"]))
     assert out[-1][3].all()
     return out, tol
+
+
+def test_operators_on_chip():
+    fs = _moving(S.fem_scene(seed=S.config_seed(3, 21), blocks=(17, 17, 1), nodes_per_block=(2, 2, 25)), 3)
+    a, tol = _run(fs, torch.float32, resident=True, form=35)
+    b, _ = _run(fs, torch.float32, tol, resident=False, form=0)
+    for (xa, ia, ta, ca), (xb, ib, tb, cb) in zip(a, b):
+        np.testing.assert_array_equal(ia, ib)
+        np.testing.assert_array_equal(ta, tb)
+        for x, y in zip(xa, xb):
+            np.testing.assert_array_equal(x, y)
 
 
 @pytest.mark.parametrize("dtype,bodies,nodes", [(torch.float64, 58, (2, 2, 25)), (torch.float32, 114, (2, 2, 27))])
