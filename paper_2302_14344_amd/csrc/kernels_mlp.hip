@@ -14,7 +14,10 @@
 // (tile rows padded to 80 bytes, which keeps those reads 16-byte aligned and spreads the rows
 // over the banks).  Epilogues fuse the bias, the ReLU and the BF16 store of the next layer's
 // input, or the ReLU mask of the backward pass.
+#include <type_traits>
+
 #include "mlp_internal.hpp"
+#include "row_walk.hpp"
 
 namespace subadmm {
 
@@ -159,6 +162,7 @@ hipError_t launch_gemm(const GemmArgs<TA, TB>& g, int splits, hipStream_t s) {
 // ------------------------------------------------------------------------------------
 constexpr int kFusedLd = kFusedWidth + 8;  // 528-byte rows: 16-byte aligned fragment reads
 constexpr int kFusedThreads = 512;
+constexpr unsigned kFusedResident = 512;  // workgroups of that size the device holds at once (two a CU)
 constexpr int kKBlocks = kFusedWidth / 32;
 
 __device__ inline bf16x8_t load8(const uint16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
@@ -172,16 +176,17 @@ __device__ inline bf16x8_t frag(const uint16_t* W, int nt, int N, int s, int K, 
 }
 
 // rows 0..31 of buf (width entries, zero padded) to rows r0.. of dst (ld entries per row)
+template <int kThreads>
 __device__ inline void store_rows(const uint16_t (*buf)[kFusedLd], uint16_t* dst, long r0, long rows, int width) {
   const int ld = mlp_ld(width), nv = ld >> 3;
-  for (int q = threadIdx.x; q < kFusedRows * nv; q += kFusedThreads) {
+  for (int q = threadIdx.x; q < kFusedRows * nv; q += kThreads) {
     const int r = q / nv, c = (q - r * nv) << 3;
     if (r0 + r < rows) *reinterpret_cast<uint4*>(dst + (r0 + r) * ld + c) = *reinterpret_cast<const uint4*>(&buf[r][c]);
   }
 }
 
-template <bool kKeep>
-__global__ void __launch_bounds__(kFusedThreads, 4) mlp_forward_kernel(MlpFusedArgs a) {
+template <bool kKeep, int kThreads>
+__global__ void __launch_bounds__(kThreads, 4) mlp_forward_kernel(MlpFusedArgs a) {
   __shared__ __align__(16) uint16_t buf[2][kFusedRows][kFusedLd];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid) >> 6;
   const int g = lane >> 4, cl = lane & 15;
@@ -207,7 +212,7 @@ __global__ void __launch_bounds__(kFusedThreads, 4) mlp_forward_kernel(MlpFusedA
   {
     // input rows, zero beyond the width up to the next multiple of 32 and beyond the batch
     const int w0 = a.net.w[0], kp = (w0 + 31) / 32 * 32;
-    for (int q = tid; q < kFusedRows * kp; q += kFusedThreads) {
+    for (int q = tid; q < kFusedRows * kp; q += kThreads) {
       const int r = q / kp, c = q - r * kp;
       uint16_t v = 0;
       if (r0 + r < a.batch && c < w0) {
@@ -218,7 +223,7 @@ __global__ void __launch_bounds__(kFusedThreads, 4) mlp_forward_kernel(MlpFusedA
     }
   }
   __syncthreads();
-  if (kKeep) store_rows(buf[0], a.act + a.net.off_act[0], r0, a.batch, a.net.w[0]);
+  if (kKeep) store_rows<kThreads>(buf[0], a.act + a.net.off_act[0], r0, a.batch, a.net.w[0]);
   int cur = 0;
   for (int l = 0; l < a.net.L; ++l) {
     const int K = a.net.w[l], N = a.net.w[l + 1];
@@ -268,18 +273,32 @@ __global__ void __launch_bounds__(kFusedThreads, 4) mlp_forward_kernel(MlpFusedA
     fetch_bias(l + 1);
     __syncthreads();
     cur = nxt;
-    if (kKeep) store_rows(buf[cur], a.act + a.net.off_act[l + 1], r0, a.batch, N);
+    if (kKeep) store_rows<kThreads>(buf[cur], a.act + a.net.off_act[l + 1], r0, a.batch, N);
   }
 }
 
 hipError_t launch_fused_forward(const MlpFusedArgs& a, hipStream_t s) {
   if (a.batch <= 0) return hipSuccess;
   const dim3 grid((unsigned)((a.batch + kFusedRows - 1) / kFusedRows));
-  if (a.act)
-    hipLaunchKernelGGL(mlp_forward_kernel<true>, grid, dim3(kFusedThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL(mlp_forward_kernel<false>, grid, dim3(kFusedThreads), 0, s, a);
-  return hipGetLastError();
+  const auto go = [&](auto threads) -> hipError_t {
+    constexpr int T = decltype(threads)::value;
+    if (a.act)
+      hipLaunchKernelGGL((mlp_forward_kernel<true, T>), grid, dim3(T), 0, s, a);
+    else
+      hipLaunchKernelGGL((mlp_forward_kernel<false, T>), grid, dim3(T), 0, s, a);
+    return hipGetLastError();
+  };
+  // A wave owns 32 columns, so narrow layers leave most of eight waves without products; with no more
+  // waves than the widest layer needs twice as many workgroups are resident (four, by LDS).  While the
+  // grid fits the device at once, and in a single layer, the idle waves help with the rows instead.
+  // Inference of 65,536 rows: 12-64-64-6 36.8 us with eight waves and 28.7 with two, 12-100-100-6
+  // 37.8 and 24.0 with four; 40-9 17.8 with eight and 20.3 with two.
+  int w = 0;
+  for (int k = 1; k <= a.net.L; ++k) w = a.net.w[k] > w ? a.net.w[k] : w;
+  const bool fewer = grid.x > kFusedResident && a.net.L > 1;
+  if (fewer && w <= 64) return go(std::integral_constant<int, 128>{});
+  if (fewer && w <= 128) return go(std::integral_constant<int, 256>{});
+  return go(std::integral_constant<int, kFusedThreads>{});
 }
 
 // ------------------------------------------------------------------------------------
@@ -628,11 +647,12 @@ template hipError_t launch_gemm<float, float>(const GemmArgs<float, float>&, int
 // an affine map); y rows of ldy entries.
 __global__ void cast_rows_kernel(const float* x, const float* scale, const float* shift, long rows, int width,
                                  uint16_t* y, int ldy) {
-  const long n = rows * width;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const long r = i / width;
-    const int c = (int)(i - r * width);
-    y[r * ldy + c] = scale ? to_bf16(x[i] * scale[c] + shift[c]) : to_bf16(x[i]);
+  // row and column by carry: a 64-bit division per entry cost 2% of a 300-256-7 network's pass
+  const long n = rows * width, step = (long)gridDim.x * blockDim.x;
+  RowWalk at((int)(blockIdx.x * blockDim.x + threadIdx.x), (int)step, width);
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step, at.next()) {
+    const int c = at.col;
+    y[(long)at.row * ldy + c] = scale ? to_bf16(x[i] * scale[c] + shift[c]) : to_bf16(x[i]);
   }
 }
 
