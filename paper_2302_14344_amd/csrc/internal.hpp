@@ -13,7 +13,7 @@ enum : int32_t { FLAG_NOT_SPD = 1, FLAG_NONFINITE = 2, FLAG_BARRIER = 4 };
 enum : int32_t { KIND_EQUALITY = 0, KIND_CONTACT = 1, KIND_HARD_INEQ = 2, KIND_SOFT = 3 };
 
 constexpr int kMaxDof = 64;      // largest subsystem of the rigid model's kernels
-constexpr int kMaxFactorDof = 512;  // largest subsystem of the factorisation (a thread per column)
+constexpr int kMaxFactorDof = 512;  // largest subsystem of the factorisation
 constexpr int kMaxFemDof = 768;  // largest subsystem (FEM block path)
 // Copies of the FEM scene's residual totals (a workgroup reads the copy of its index mod
 // kPartCopies, so the lines every workgroup polls are spread over more addresses).

@@ -1552,8 +1552,8 @@ hipError_t launch_factor(const FactorArgs<T>& a, int count, int max_n, int max_n
       hipLaunchKernelGGL((factor_wave_kernel<T, T>), dim3(blocks), dim3(256), 4 * slice, s, a, count, (int)slice);
     return hipGetLastError();
   }
-  // a class of few subsystems (the largest ones) is latency-bound: give each more threads;
-  // at least one thread per trailing column of the Cholesky factor's first step (n - 1)
+  // a class of few subsystems (the largest ones) is latency-bound: give each more threads; so
+  // are subsystems of more DOFs than that, whose LDS leaves room for one workgroup per CU
   int threads = count < 256 ? 512 : count < 2048 ? 256 : 128;
   if (max_n > kMaxFactorDof) return hipErrorInvalidValue;
   while (threads < max_n - 1) threads *= 2;
