@@ -101,8 +101,8 @@ __device__ inline C tile_at(P p, int i, bool in) {
 // Bound by latency: the diagonal tiles (~2.7 us each, one wave) and chains of tile products; few
 // subsystems leave the matrix cores mostly idle.  Measured against the column-by-column form
 // (a barrier per column of the factor and per four pivot rows of the substitutions): 48 DOF with
-// 75 slot rows 78 -> 34 us, 127 DOF 260 -> 89 us, 285 DOF in device memory 4790 -> 483 us; the
-// legged batch's classes 80 -> 46 us and 85 -> 64 us (one subsystem per wave).
+// 75 slot rows 78 -> 33 us, 127 DOF 260 -> 86 us, 285 DOF in device memory 4790 -> 462 us; the
+// legged batch's classes, side by side, 80 -> 57 us and 85 -> 66 us (one subsystem per wave).
 template <typename T, typename C, typename Grp = GroupWg, typename P = C*, int kUnroll = 1>
 __device__ __attribute__((always_inline)) inline void factor_body(const FactorArgs<T>& a, const int i, P sm,
                                                                  double (*red)[16], int& bad) {
@@ -530,7 +530,7 @@ __device__ inline void z_update_multi(const LoopArgs<T>& a, const int j, const i
 // topology from device memory.  Same arithmetic in the same order.  A dependent chain of
 // device-memory reads (member, slot, penalty, division) set the iteration's time before: one
 // solve of 200 ragged scenes with couplings of up to four members, FP32, 1248 us
-// without the descriptors and 735 us with them.
+// without the descriptors and 735 us with them (686 since rows go three at a time).
 template <typename T>
 struct MultiDesc {
   T ib[kMaxMembers];
