@@ -375,8 +375,8 @@ int subadmm_rigid_step_graph(subadmm_problem* p, void* pos, void* rot, void* vel
  * steps by one workgroup without waiting for the other scenes between steps, so the launch
  * takes as long as the scene whose iterations summed over the steps are the most, not the
  * sum over the steps of each step's slowest scene.  The factorisation and iteration are the
- * per-step kernels' (thread-per-slot-row form, rows not split; the options of the iteration
- * kernel form do not apply).  Statistics: iters, converged, theta and r_theta of the last
+ * per-step kernels' (thread-per-slot-row form; SUBADMM_OPT_SPLIT_ROWS = 2 applies, the other
+ * options of the iteration kernel form do not).  Statistics: iters, converged, theta and r_theta of the last
  * step; the totals count every step.  v_hat and lambda (optional) receive the last step's
  * values.  E_ARG for another warm mode or n_steps < 1. */
 int subadmm_rigid_steps(subadmm_problem* p, void* pos, void* rot, void* vel, void* omega, double dt,
